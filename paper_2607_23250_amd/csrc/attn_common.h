@@ -233,6 +233,33 @@ __host__ __device__ __forceinline__ int swt(int row, int col) {
   }
 }
 
+// Place (in elements) of 16-byte chunk `col` of row `row` of a K / V tile whose
+// copies land as 1 KiB units of 64 / C whole rows (one wave load each).  The
+// places inside a unit are permuted so that row reads (16 rows at one chunk)
+// and transpose reads (4 rows x 4 chunks) both touch every bank once, as with
+// swt; but here chunks 4 apart and rows 16 apart lie at fixed distances, so
+// every operand read of a tile is one of two per-lane addresses plus an
+// immediate, instead of one address register (and one address addition per
+// key block) for each chunk.  Four neighbouring lanes of a copy still read 64
+// contiguous bytes of one row: with four rows there, the forward of the 1M
+// share took 20% longer.
+template <int C>
+__host__ __device__ __forceinline__ int swu(int row, int col) {
+  static_assert(C == 8 || C == 16, "tiles of 64 or 128 bf16 per row");
+  constexpr int R = 64 / C;   // rows of a unit
+  return 512 * (row / R) +
+         8 * (4 * R * (col >> 2) + 4 * (row % R) + ((col & 3) ^ ((row >> 2) & 3)));
+}
+// The row and chunk of a tile at place `l` (in chunks) of unit `u`.
+template <int C>
+__device__ __forceinline__ int swu_row(int u, int l) {
+  return (64 / C) * u + (l >> 2) % (64 / C);
+}
+template <int C>
+__device__ __forceinline__ int swu_col(int u, int l) {
+  return 4 * (l / (4 * (64 / C))) + ((l & 3) ^ ((swu_row<C>(u, l) >> 2) & 3));
+}
+
 // gfx950 LDS transpose read (ds_read_b64_tr_b16).  Within each group of 16
 // lanes, lane 4r + e receives as element i the 16-bit element e of the
 // 8 bytes addressed by lane 4i + r of the same group: 16 lanes that address

@@ -281,28 +281,27 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
   const int tid = threadIdx.x, l = tid & 63, ln = l & 31, kg = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index (uniform)
   int q_serve = xcd_of_workgroup(), q_left = kXcds;
-  // per-lane LDS offsets (elements) of the operand reads, fixed for the kernel
-  // K rows perm32(ln) for S^T; transpose reads of the V tile for the V^T
-  // operand of O^T (rows = keys, as in the dQ kernel's K^T)
+  // per-lane LDS offsets (elements) of the operand reads, fixed for the kernel:
+  // K rows perm32(ln) for S^T (chunk 2 c + kg: one offset per parity of c, then
+  // 4 chunks per 2 steps of c), and the transpose reads of the V tile for the
+  // V^T operand of O^T (rows = keys, as in the dQ kernel's K^T; one offset per
+  // half, then 4 chunks per step of dt)
+  constexpr int STEP4 = S::KC == 16 ? 128 : 256;   // elements from chunk j to chunk j + 4
   const int prow = perm32(ln);
-  int koff[D / 16], troff[D / 32][2];
-  static_for<D / 16>([&](auto c) { koff[c] = prow * D + 8 * swt<S::KC>(prow, 2 * c + kg); });
+  const int koff[2] = {swu<S::KC>(prow, kg), swu<S::KC>(prow, 2 + kg)};
+  int troff[2];
   {
     const int grp = l >> 4, i = (l & 15) >> 2, r = l & 3;
-    static_for<D / 32>([&](auto dt) {
-      static_for<2>([&](auto hf) {
-        const int row = 8 * (grp >> 1) + 4 * hf + i;
-        const int chunk = 4 * dt + 2 * (grp & 1) + (r & 1);
-        troff[dt][hf] = row * D + 8 * swt<S::KC>(row, chunk) + 4 * (r >> 1);
-      });
+    static_for<2>([&](auto hf) {
+      troff[hf] = swu<S::KC>(8 * (grp >> 1) + 4 * hf + i, 2 * (grp & 1) + (r & 1)) + 4 * (r >> 1);
     });
   }
-  // staging: wave load u covers rows (w + 4u) * 64 / KC + l / KC of a tile;
-  // k_lane[u] is the lane's byte offset from the block's first K (V) row
+  // staging: wave load u fills unit w + 4 u of a tile; k_lane[u] is the lane's
+  // byte offset from the block's first K (V) row
   uint32_t k_lane[S::NK];
   static_for<S::NK>([&](auto u) {
-    const int r = (w + kWaves * u) * (64 / S::KC) + l / S::KC;
-    k_lane[u] = 2u * (uint32_t)(r * h_kv * D + 8 * swt<S::KC>(r, l % S::KC));
+    const int wl = w + kWaves * u;
+    k_lane[u] = 2u * (uint32_t)(swu_row<S::KC>(wl, l) * h_kv * D + 8 * swu_col<S::KC>(wl, l));
   });
 
   for (;;) {
@@ -358,9 +357,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
       // the last block of the buffer: keys past it read the last key (masked)
       static_for<S::NK>([&](auto u) {
         const int wl = w + kWaves * u;
-        const int r = wl * (64 / S::KC) + l / S::KC;
-        const int col = swt<S::KC>(r, l % S::KC);
-        int64_t key = key0 + (int64_t)b * kFwdBN + r;
+        const int col = swu_col<S::KC>(wl, l);
+        int64_t key = key0 + (int64_t)b * kFwdBN + swu_row<S::KC>(wl, l);
         key = key < n_kv ? key : n_kv - 1;
         g2l16(src + ((size_t)key * h_kv + it.g) * D + 8 * col, dst + wl * 512);
       });
@@ -368,7 +366,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
 
     issue(kb0, 0, 0);
     issue(kb0, 0, 1);
-    wait_vm();
+    wait_vm_known();   // also Q: no wait for it inside the loop
     __syncthreads();
     for (int b = kb0; b < nkb; ++b) {
       const int buf = (b - kb0) & 1;
@@ -382,15 +380,30 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
         issue(b + 1, buf ^ 1, 1);
       }
       if (b < wave_nkb) {
+        constexpr int NC = D / 16, NT = D / 32, AHEAD = 4;
         const bf16 *Ks = smem + buf * S::STAGE;
         const bf16 *Vs = Ks + S::K_EL;
+        // S^T: every operand is read AHEAD products before the one that takes
+        // it.  Left to itself the compiler reads many of them right before
+        // their product and waits for the LDS round trip, as often as 32 times
+        // per block.  On the 1M share: 430 ms, 420 with the reads ahead here
+        // and in O^T, 413 with the swu places too (1167 of the 1560 TFLOP/s
+        // that a large matrix product reaches); at 32K tokens 3.18, 3.07, 3.06.
         f32x16 s[2];
-        static_for<2>([&](auto t) {
-          static_for<16>([&](auto r) { s[t][int(r)] = 0.f; });
-          const bf16 *kp = Ks + 32 * t * D;
-          static_for<D / 16>([&](auto c) {
-            s[t] = mfma32(*reinterpret_cast<const bf16x8 *>(kp + koff[c]), qf[c], s[t]);
-          });
+        bf16x8 kop[2 * NC];   // product i: key tile i / NC, chunk i % NC
+        const bf16 *kp[2] = {Ks + koff[0], Ks + koff[1]};
+        auto rd = [&](auto i) {
+          constexpr int t = i / NC, c = i % NC;
+          kop[i] = *reinterpret_cast<const bf16x8 *>(kp[c & 1] + 32 * t * D + (c >> 1) * STEP4);
+        };
+        static_for<AHEAD>([&](auto i) { rd(i); });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<2 * NC>([&](auto i) {
+          constexpr int t = i / NC, c = i % NC;
+          if constexpr (c == 0) static_for<16>([&](auto r) { s[t][int(r)] = 0.f; });
+          s[t] = mfma32(kop[i], qf[c], s[t]);
+          if constexpr (i + AHEAD < 2 * NC) rd(std::integral_constant<int, i + AHEAD>{});
+          __builtin_amdgcn_sched_barrier(0);
         });
         if (more) issue(b + 1, buf ^ 1, 0);
         // keys past the row are masked only in blocks that reach past the
@@ -440,14 +453,22 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
           expo(-m_run);
         }
         l_run += ps;
+        constexpr int TA = 4;
+        bf16x8 vop[4 * NT];
+        const bf16 *vp[2] = {Vs + troff[0], Vs + troff[1]};
+        auto rt = [&](auto j) {
+          constexpr int at = 16 * D * (j / NT) + STEP4 * (j % NT);
+          vop[j] = lds_tr16x2(vp[0] + at, vp[1] + at);
+        };
+        static_for<TA>([&](auto j) { rt(j); });
         if (more) issue(b + 1, buf ^ 1, 1);
-        // O^T += V^T P^T; key chunk c = 16 keys from tile row 16 c
-        static_for<D / 32>([&](auto dt) {
-          static_for<4>([&](auto c) {
-            const bf16 *base = Vs + 16 * c * D;
-            oacc[dt] = mfma32(lds_tr16x2(base + troff[dt][0], base + troff[dt][1]), pf[c],
-                              oacc[dt]);
-          });
+        __builtin_amdgcn_sched_barrier(0);
+        // O^T += V^T P^T; product j takes key chunk j / NT (16 keys from tile
+        // row 16 j / NT), 32 columns j % NT, its operand read TA products ahead
+        static_for<4 * NT>([&](auto j) {
+          oacc[j % NT] = mfma32(vop[j], pf[j / NT], oacc[j % NT]);
+          if constexpr (j + TA < 4 * NT) rt(std::integral_constant<int, j + TA>{});
+          __builtin_amdgcn_sched_barrier(0);
         });
       }
       wait_vm();
