@@ -34,9 +34,6 @@
 
 namespace libra {
 
-__device__ __forceinline__ int32_t ld_agent(const int32_t *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ unsigned long long ld_agent(const unsigned long long *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -57,7 +54,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_bwd_kernel(
     const int64_t *__restrict__ cu, int64_t n, const libra_tile_t *__restrict__ tiles, int64_t T,
     int h_q, int h_kv, int64_t n_q, int64_t n_kv, int32_t *__restrict__ hdr,
     int32_t *__restrict__ ext, unsigned long long *__restrict__ gmask,
-    BwdItem *__restrict__ items, int64_t max_items) {
+    BwdItem *__restrict__ items, int64_t max_items, int grid) {
   __shared__ int32_t hist[kXcds * kQBuckets];
   __shared__ int32_t part[kPrepThreads];
   const int tid = threadIdx.x;
@@ -135,7 +132,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_bwd_kernel(
           for (int kb = tid; kb < nkb; kb += kPrepThreads) emit(f, j, e, g, kb);
     }
   };
-  build_queues<BwdItem>(each, hist, part, hdr, kBwdQ, items, max_items);
+  build_queues<BwdItem>(each, hist, part, hdr, kBwdQ, items, max_items, grid);
 }
 
 // ---------------------------------------------------------------------------
@@ -459,7 +456,8 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index (uniform)
   const int G = h_q / h_kv;
   const int64_t nblk = nq_pad / kRows;
-  int q_serve = xcd_of_workgroup(), q_left = kXcds;
+  const int q_serve = xcd_of_workgroup();
+  int q_state = kTakeFirst;
   // per-lane LDS offsets (elements) of the operand reads: rows of Q / dO for
   // S and dP (row perm32(ln), 8 columns), and the transpose reads that give
   // dO^T / Q^T for dV^T and dK^T: this lane addresses 4 columns of row
@@ -500,7 +498,10 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
   const float dk_mul = scale / (s_q * s_o * s_v), dv_mul = 1.f / s_o;
 
   for (;;) {
-    if (tid == 0) s_item = take_item(hdr, kBwdQ, q_serve, q_left);
+    if (w == 0) {
+      const int got = take_item(hdr, kBwdQ, q_serve, q_state);
+      if (tid == 0) s_item = got;
+    }
     __syncthreads();
     const int idx = __builtin_amdgcn_readfirstlane(s_item);
     if (idx < 0) break;
@@ -681,6 +682,9 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
       ++issued;
     };
     while (iss.valid && issued < S::NSTAGE - 1) issue_next();
+    // of the eight places modulo 32 bytes this one was the best: 100.1 ms on the
+    // 256K share against 100.8 to 102.7
+    align_code<1>();
     while (computed < issued) {
       // keep up to NSTAGE - 1 steps in flight, the one computed now included
       if (iss.valid && issued < computed + S::NSTAGE - 1) issue_next();
@@ -806,11 +810,11 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
     hipLaunchKernelGGL(zero_kernel, dim3(blocks), dim3(256), 0, st, static_cast<uint4 *>(dv), n16);
   }
   if (T > 0) {
-    hipLaunchKernelGGL(prep_bwd_kernel, dim3(1), dim3(kPrepThreads), 0, st, cu, n, tiles, T, h_q,
-                       h_kv, n_q, n_kv, hdr, ext, gmask, items, L.max_items);
     int dev = 0, cus = 256;
     hipGetDevice(&dev);
     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    hipLaunchKernelGGL(prep_bwd_kernel, dim3(1), dim3(kPrepThreads), 0, st, cu, n, tiles, T, h_q,
+                       h_kv, n_q, n_kv, hdr, ext, gmask, items, L.max_items, cus);
     // the dQ kernel runs one workgroup per CU; its items split K like the
     // forward's when there are few of them
     auto *splits = reinterpret_cast<FwdSplit *>(ws + L.splits);

@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_fwd_kernel(
       }
     });
   };
-  build_queues<FwdItem>(each, hist, part, hdr, kFwdQ, items, max_items);
+  build_queues<FwdItem>(each, hist, part, hdr, kFwdQ, items, max_items, grid);
   __syncthreads();
   if (tid == 0) {
     hdr[kFwdSplits] = s_nsplit;
@@ -280,7 +280,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
   __shared__ int32_t s_item;
   const int tid = threadIdx.x, l = tid & 63, ln = l & 31, kg = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index (uniform)
-  int q_serve = xcd_of_workgroup(), q_left = kXcds;
+  const int q_serve = xcd_of_workgroup();
+  int q_state = kTakeFirst;
   // per-lane LDS offsets (elements) of the operand reads, fixed for the kernel:
   // K rows perm32(ln) for S^T (chunk 2 c + kg: one offset per parity of c, then
   // 4 chunks per 2 steps of c), and the transpose reads of the V tile for the
@@ -305,7 +306,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
   });
 
   for (;;) {
-    if (tid == 0) s_item = take_item(hdr, kFwdQ, q_serve, q_left);
+    if (w == 0) {
+      const int got = take_item(hdr, kFwdQ, q_serve, q_state);
+      if (tid == 0) s_item = got;
+    }
     __syncthreads();
     const int idx = __builtin_amdgcn_readfirstlane(s_item);
     if (idx < 0) break;

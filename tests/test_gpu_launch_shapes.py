@@ -1,0 +1,64 @@
+"""GPU parity where the launch shape can go wrong: how many work items there
+are, in which of the queues, and how they fall on the workgroups.
+
+Against the float64 oracle at the fixed bounds of gpu_util.check.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2607_23250_amd as pl
+from oracle import attention as oa
+import workloads as wl
+from gpu_util import DEV, LSE_TOL, check, say, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _tiles(spans):
+    """Tiles (q_begin, q_end, head_begin, head_end), rows at their positions."""
+    t = np.zeros(len(spans), dtype=pl.TILE_DTYPE)
+    for i, (a, b, h0, h1) in enumerate(spans):
+        t[i]["q_begin"], t[i]["q_end"], t[i]["q_row"] = a, b, a
+        t[i]["head_begin"], t[i]["head_end"] = h0, h1
+    return t
+
+
+def _check(lengths, tiles, h_q, h_kv, d, seed=5):
+    """fwd + accumulate-mode bwd of `tiles` (one head range over all rows)."""
+    n = sum(lengths)
+    q, k, v, do = wl.tensors(seed, n, n, h_q, h_kv, d)
+    qd, kd, vd, dod = (t.to(DEV) for t in (q, k, v, do))
+    cu = torch.from_numpy(np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)).to(DEV)
+    td = pl.tiles_to_device(tiles, DEV)
+    o, lse = pl.libra_attn_fwd(qd, kd, vd, cu, td)
+    dq, dk, dv = pl.libra_attn_bwd(qd, kd, vd, o, lse, dod, cu, td, accumulate=True)
+    torch.cuda.synchronize()
+    h0, h1 = int(tiles["head_begin"][0]), int(tiles["head_end"][0])
+    g0, g1 = h0 * h_kv // h_q, (h1 - 1) * h_kv // h_q + 1
+    G = h_q // h_kv
+    assert h0 % G == 0 and h1 % G == 0, "whole KV groups"
+    sl = (slice(None), slice(h0, h1))
+    kv = (slice(None), slice(g0, g1))
+    pos = np.arange(n)
+    O, LSE = oa.attention_fwd(q[sl], k[kv], v[kv], lengths, pos)
+    dQ, dK, dV = oa.attention_bwd(q[sl], k[kv], v[kv], do[sl], lengths, pos)
+    check("O", to_np(o)[sl], O, bf16_out=True)
+    check("LSE", to_np(lse)[h0:h1], LSE, (LSE_TOL, 1e-4))
+    check("dQ", to_np(dq)[sl], dQ, bf16_out=True)
+    check("dK fp32", to_np(dk)[kv], dK)
+    check("dV fp32", to_np(dv)[kv], dV)
+    other = [g for g in range(h_kv) if not g0 <= g < g1]
+    assert not to_np(dk)[:, other].any() and not to_np(dv)[:, other].any()
+
+
+@pytest.mark.parametrize("n_items", (1, 32, 33, 64, 65, 700))
+def test_one_queue_holds_every_item(n_items):
+    """One of eight heads (no grouping): all items lie in one queue.  With more
+    of them than its own workgroups (64 of the forward, 32 of the backward) the
+    others have to come from the seven empty queues; with fewer, every
+    workgroup has to find its way out."""
+    lengths = [int(x) for x in np.random.default_rng(n_items).integers(1, 60, n_items)]
+    n = sum(lengths)
+    say(f"[one queue] {n_items} items of one head, {n} rows")
+    _check(lengths, _tiles([(0, n, 3, 4)]), 8, 8, 64)
