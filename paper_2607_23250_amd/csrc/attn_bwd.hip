@@ -12,11 +12,21 @@
 //     loops over the 32-row query blocks of the tiles that attend them, two
 //     query heads of the KV group per step.  S and dP are computed with
 //     queries on M (lane = key), exactly the operand layout that dV^T = dO^T P
-//     and dK^T = Q^T dS need; the dO^T / Q^T operands come from the same
-//     row-major LDS tiles through the LDS transpose reads.  LSE and D enter
-//     the S and dP products as one extra k-block (see bwd_pre_kernel), so the
-//     VALU only exponentiates and multiplies.  Steps are staged in a 4-deep
-//     LDS ring, two ahead of the one computed.
+//     and dK^T = Q^T dS need; the dO^T / Q^T operands come from the same LDS
+//     tiles through the LDS transpose reads.  LSE and D enter the S and dP
+//     products as one extra k-block (see bwd_pre_kernel), so the VALU only
+//     exponentiates and multiplies.  A step's Q, dO and extra operands are two
+//     contiguous records that the pre-pass lays out as the LDS stage wants
+//     them; steps are staged in a 4-deep LDS ring, three ahead of the one
+//     computed.
+//     One wave per SIMD issues everything, so the kernel is bound by its
+//     instruction stream and by the products (1.30 PFLOP/s of them on the
+//     256K share, against 1.56 of a large matrix product).  dK / dV on the
+//     256K share, same box: row-major copies 98.9 ms (about 850 instructions
+//     per step, 66 of them address additions, 58 spilled scalars); records
+//     93.3; the copies posted between the product phases instead of at the top
+//     91.4 to 92.9; the two heads of a step pipelined against one another
+//     (about 490 instructions) 3% less again.
 //   * dQ (attn_bwd_dq.hip), query-stationary, shaped like the forward.  It
 //     recomputes S and dP instead of accumulating dQ across key blocks with
 //     atomics: on long samples that accumulation is read-modify-write traffic
@@ -38,10 +48,14 @@ __device__ __forceinline__ unsigned long long ld_agent(const unsigned long long 
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Bit set of the KV heads whose query groups intersect [hb, he).
-__device__ __forceinline__ unsigned long long group_bits(int hb, int he, int G) {
+// Bit set of the KV heads whose query groups intersect [hb, he); `odd` is set
+// if it covers an odd number of heads of one of them.
+__device__ __forceinline__ unsigned long long group_bits(int hb, int he, int G, bool &odd) {
   unsigned long long m = 0;
-  for (int g = hb / G; g * G < he; ++g) m |= 1ull << g;
+  for (int g = hb / G; g * G < he; ++g) {
+    m |= 1ull << g;
+    odd |= ((min(he, (g + 1) * G) - max(hb, g * G)) & 1) != 0;
+  }
   return m;
 }
 
@@ -64,21 +78,23 @@ __global__ __launch_bounds__(kPrepThreads) void prep_bwd_kernel(
     __hip_atomic_store(&ext[j], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&gmask[j], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (tid < 5) {
-    // the skipped-tile count (counted here for the backward) and the max |x| slots
-    __hip_atomic_store(&hdr[tid == 0 ? (int)kBadTiles : kMaxAbs + tid - 1], 0, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+  if (tid < 6) {
+    // the skipped-tile count (counted here for the backward), the odd-heads
+    // flag and the max |x| slots
+    __hip_atomic_store(&hdr[tid == 0 ? (int)kBadTiles : tid == 1 ? (int)kOddHeads : kMaxAbs + tid - 2],
+                       0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __threadfence();
   __syncthreads();
   int bad = 0;
+  bool odd = false;
   for (int64_t t = tid; t < T; t += kPrepThreads) {
     const libra_tile_t tl = tiles[t];
     if (!tile_ok(tl, n_q, n_kv, h_q)) {
       ++bad;
       continue;
     }
-    const unsigned long long bits = group_bits(tl.head_begin, tl.head_end, G);
+    const unsigned long long bits = group_bits(tl.head_begin, tl.head_end, G, odd);
     for (int64_t j = upper_bound64(cu, n, tl.q_begin) - 1; j < n && cu[j] < tl.q_end; ++j) {
       const int64_t pe = tl.q_end < cu[j + 1] ? tl.q_end : cu[j + 1];
       atomicMax(&ext[j], (int32_t)(pe - cu[j]));
@@ -86,6 +102,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_bwd_kernel(
     }
   }
   if (bad) atomicAdd(&hdr[kBadTiles], bad);
+  if (odd) atomicOr(&hdr[kOddHeads], 1);
   __threadfence();
   __syncthreads();
   // Samples with more than kCoopBlocks key blocks are enumerated by the
@@ -183,15 +200,15 @@ __device__ __forceinline__ float absmax8(const bf16x8 &x) {
 constexpr int kTileSplit = 64;
 
 // Per tile (kTileSplit workgroups each): max |Q| and max |dO| over the
-// covered (row, head) pairs; and, in the fp16 copies, zeros for the rows of
-// the tile's first and last 32-row blocks that lie outside the tile (the
-// dK / dV kernel stages whole blocks; rows no tile covers must hold finite
-// values, since they meet P = dS = 0 in its products).
+// covered (row, head) pairs; and, in the records, zeros for the rows of the
+// tile's first and last 32-row blocks that lie outside the tile (the dK / dV
+// kernel stages whole records; rows no tile covers must hold finite values,
+// since they meet P = dS = 0 in its products).
 template <int D>
 __global__ __launch_bounds__(256) void bwd_absmax_q_kernel(
     const bf16 *__restrict__ q, const bf16 *__restrict__ dout,
     const libra_tile_t *__restrict__ tiles, int h_q, int64_t n_q, int64_t n_kv,
-    int32_t *__restrict__ hdr, f16 *__restrict__ q16, f16 *__restrict__ do16) {
+    int32_t *__restrict__ hdr, f16 *__restrict__ rec) {
   const int tid = threadIdx.x;
   const libra_tile_t tl = tiles[blockIdx.x / kTileSplit];
   if (!tile_ok(tl, n_q, n_kv, h_q)) return;
@@ -201,20 +218,26 @@ __global__ __launch_bounds__(256) void bwd_absmax_q_kernel(
   for (int64_t m = ra / kRows + blockIdx.x % kTileSplit; m * kRows < rb; m += kTileSplit) {
     const int64_t row = m * kRows + r;
     const bool ok = row >= ra && row < rb;
-    if (!ok && row >= n_q) continue;
     for (int h = tl.head_begin; h < tl.head_end; ++h) {
-      const size_t off = ((size_t)row * h_q + h) * D + part * (D / 8);
-      static_for<D / 64>([&](auto c) {
-        if (ok) {
+      if (ok) {
+        const size_t off = ((size_t)row * h_q + h) * D + part * (D / 8);
+        static_for<D / 64>([&](auto c) {
           mq = fmaxf(mq, absmax8(*reinterpret_cast<const bf16x8 *>(q + off + 8 * c)));
           mo = fmaxf(mo, absmax8(*reinterpret_cast<const bf16x8 *>(dout + off + 8 * c)));
-        } else {
-          f16x8 z;
-          static_for<8>([&](auto i) { z[int(i)] = f16(0.f); });
-          *reinterpret_cast<f16x8 *>(q16 + off + 8 * c) = z;
-          *reinterpret_cast<f16x8 *>(do16 + off + 8 * c) = z;
-        }
+        });
+        continue;
+      }
+      f16 *rp = rec + ((size_t)m * h_q + h) * rec_els(D);
+      f16x8 z;
+      static_for<8>([&](auto i) { z[int(i)] = f16(0.f); });
+      static_for<D / 64>([&](auto c) {
+        const int at = rec_at(r, part * (D / 64) + c);
+        *reinterpret_cast<f16x8 *>(rp + at) = z;
+        *reinterpret_cast<f16x8 *>(rp + kRows * D + at) = z;
       });
+      // the row's lanes of both augmented operands
+      if (part < 4)
+        *reinterpret_cast<f16x8 *>(rp + 2 * kRows * D + part * (kAugEl / 4) + 8 * perm32(r)) = z;
     }
   }
   block_max2_to(mq, mo, &hdr[kMaxAbs + 0], &hdr[kMaxAbs + 1]);
@@ -273,25 +296,23 @@ __global__ __launch_bounds__(256) void bwd_kv_pass_kernel(
 }
 
 // Pre-pass over the covered (row, head) pairs, 32 rows at a time:
-//   * the fp16 copies of Q and dO (scaled, see above);
-//   * per 32-row block of each head, the 32 values LSE * log2(e) followed by
-//     the 32 values D = rowsum(dO * O) for the dQ kernel ("stats",
-//     [h_q][nq_pad / 32][64] floats, so one 256-byte load fetches both);
-//   * for the dK / dV kernel the first of the two records of its extra
-//     16-deep k-block ("aug", [h_q][nq_pad / 32][2][64 lanes][8] fp16): MFMA
-//     A-operand lane l < 32 holds three fp16 terms summing to -LSE / scale
-//     (first record) or -D (second, written by the dQ kernel from the exact
-//     row sums) of the block's row perm32(l), in the scaled units of the
-//     copies, then zeros; lanes 32..63 hold zeros.  Against a B operand of
-//     ones in k = 0, 1, 2 the products then come out as S - LSE / scale and
-//     dP - D directly.
+//   * the records of the dK / dV kernel: the fp16 copies of Q and dO (scaled,
+//     see above) and the first of the two operands of its extra 16-deep
+//     k-block: MFMA A-operand lane l < 32 holds three fp16 terms summing to
+//     -LSE / scale (first operand) or -D (second, written by the dQ kernel
+//     from the exact row sums) of the block's row perm32(l), in the scaled
+//     units of the copies, then zeros; lanes 32..63 hold zeros.  Against a B
+//     operand of ones in k = 0, 1, 2 the products then come out as
+//     S - LSE / scale and dP - D directly;
+//   * the 32 values LSE * log2(e) followed by the 32 values D = rowsum(dO * O)
+//     of each block and head for the dQ kernel ("stats",
+//     [h_q][nq_pad / 32][64] floats, so one 256-byte load fetches both).
 template <int D>
 __global__ __launch_bounds__(256) void bwd_pre_kernel(
     const bf16 *__restrict__ q, const bf16 *__restrict__ o, const bf16 *__restrict__ dout,
     const float *__restrict__ lse, const libra_tile_t *__restrict__ tiles, int h_q,
     int64_t n_q, int64_t n_kv, int64_t nq_pad, float scale, const int32_t *__restrict__ hdr,
-    f16 *__restrict__ q16, f16 *__restrict__ do16, float *__restrict__ stats,
-    f16 *__restrict__ aug) {
+    f16 *__restrict__ rec, float *__restrict__ stats) {
   const int tid = threadIdx.x;
   const libra_tile_t tl = tiles[blockIdx.x / kTileSplit];
   if (!tile_ok(tl, n_q, n_kv, h_q)) return;
@@ -306,6 +327,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(
     const bool ok = row >= ra && row < rb;
     for (int h = tl.head_begin; h < tl.head_end; ++h) {
       float acc = 0.f;
+      f16 *rp = rec + ((size_t)m * h_q + h) * rec_els(D);
       if (ok) {
         const size_t off = ((size_t)row * h_q + h) * D + part * (D / 8);
         static_for<D / 64>([&](auto c) {
@@ -319,8 +341,9 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(
             qh[int(i)] = static_cast<f16>(static_cast<float>(qv[int(i)]) * s_q);
             dh[int(i)] = static_cast<f16>(dx * s_o);
           });
-          *reinterpret_cast<f16x8 *>(q16 + off + 8 * c) = qh;
-          *reinterpret_cast<f16x8 *>(do16 + off + 8 * c) = dh;
+          const int at = rec_at(r, part * (D / 64) + c);
+          *reinterpret_cast<f16x8 *>(rp + at) = qh;
+          *reinterpret_cast<f16x8 *>(rp + kRows * D + at) = dh;
         });
       }
       acc += __shfl_xor(acc, 1);
@@ -331,10 +354,13 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(
         const float lv = lse[(size_t)h * n_q + row];
         st[r] = lv * kLog2e;
         st[kRows + r] = acc;
-        f16 *ag = aug + ((size_t)h * (nq_pad / kRows) + m) * kAugEl + 8 * perm32(r);
         f16x8 sv;
         split3h(-lv / scale * (s_q * s_k), sv);
+        f16 *ag = rp + 2 * kRows * D + 8 * perm32(r);
         *reinterpret_cast<f16x8 *>(ag) = sv;
+        static_for<8>([&](auto i) { sv[int(i)] = f16(0.f); });
+        *reinterpret_cast<f16x8 *>(ag + kAugEl / 4) = sv;
+        *reinterpret_cast<f16x8 *>(ag + 3 * (kAugEl / 4)) = sv;
       }
     }
   }
@@ -350,37 +376,33 @@ __global__ __launch_bounds__(256) void zero_kernel(uint4 *__restrict__ p, int64_
 // dK / dV kernel.
 template <int D>
 struct KvShape {
-  static constexpr int QC = D / 8;          // 16-byte columns of a Q / dO row
   static constexpr int Q_EL = kRows * D;
-  static constexpr int F_EL = kAugEl;                         // the two augmented operands
-  static constexpr int HEAD_EL = 2 * Q_EL + F_EL;             // Q, dO, aug of one head
+  static constexpr int HEAD_EL = rec_els(D);                  // Q, dO, aug of one head
   static constexpr int STAGE_EL = 2 * HEAD_EL;                // a step is two query heads
   static constexpr int NSTAGE = 4;                            // LDS ring of steps
   static_assert((NSTAGE & (NSTAGE - 1)) == 0, "ring index by mask");
-  static constexpr int NQ = kRows * QC / 64 / kWaves;   // wave loads per Q (dO) tile
-  static constexpr int LOADS = 4 * NQ + 1;              // per wave per step
+  static constexpr int LOADS = STAGE_EL / 512 / kWaves;       // 1 KiB copies per wave per step
+  static_assert(LOADS * 512 * kWaves == STAGE_EL, "every wave copies as much");
   static constexpr size_t SMEM = NSTAGE * STAGE_EL * sizeof(bf16);
   static_assert((NSTAGE - 2) * LOADS <= 63, "vmcnt range");
 };
 
-// Walks the steps (32-row query block x query head) that attend one KV block:
-// tiles in list order, query blocks in row order, heads in order.  Per
+// Walks the steps (32-row query block x two query heads) that attend one KV
+// block: tiles in list order, query blocks in row order, heads in order.  Per
 // fragment (one tile's rows of the sample) everything a step needs is
-// precomputed, so that advancing is a few 32-bit scalar operations plus two
-// running 64-bit offsets (the Q / dO element offset and the aug offset).
+// precomputed, so that advancing is a few 32-bit scalar operations plus one
+// running 64-bit record offset.
 struct StepIter {
   const libra_tile_t *tiles;
   int64_t T, n_q, n_kv, key0, len;
-  int h_q, g, G, kloc0, D;
-  int64_t nblk;
+  int h_q, g, G, kloc0, rbytes;   // rbytes: of a record
   // fragment
-  int64_t t, row0;          // tile index; buffer row of the fragment's first 32-row block
-  int nm, lo0, hin, qb0;    // blocks; lo of block 0; hi of the last block; q_loc of row0
+  int64_t t;                // tile index
+  int nm, lo0, hin, qb0;    // blocks; lo of block 0; hi of the last block; q_loc of its row 0
   int h0, h1;
-  bool clamp_last;          // the last block runs past the end of the buffer
   // position
   int mi, h;
-  int64_t qoff, soff;       // element offset of (row0 + 32 mi, h) in Q / dO; in aug
+  int64_t rec;              // byte offset of the record of (block, h)
   bool valid;
 
   __device__ bool seek() {
@@ -399,16 +421,14 @@ struct StepIter {
       const int64_t first = fra + (kloc0 > qla ? kloc0 - qla : 0);
       if (first >= frb) continue;
       const int64_t mf = first / kRows, ml = (frb - 1) / kRows;
-      row0 = mf * kRows;
+      const int64_t row0 = mf * kRows;
       nm = (int)(ml - mf + 1);
       lo0 = (int)(fra > row0 ? fra - row0 : 0);
       hin = (int)(frb - ml * kRows);
       qb0 = (int)(qla - (fra - row0));
-      clamp_last = ml * kRows + kRows > n_q;
       mi = 0;
       h = h0;
-      qoff = (row0 * h_q + h0) * D;
-      soff = ((int64_t)h0 * nblk + mf) * kAugEl;
+      rec = (mf * h_q + h0) * rbytes;
       return true;
     }
     return false;
@@ -418,17 +438,12 @@ struct StepIter {
   // step of an odd head count
   __device__ void next() {
     if ((h += 2) < h1) {
-      qoff += 2 * D;
-      soff += 2 * nblk * kAugEl;
+      rec += 2 * rbytes;
       return;
     }
-    const int back = h - 2 - h0;                 // heads advanced within this block
+    rec += (int64_t)((h_q - (h - 2 - h0)) * rbytes);   // back by the heads advanced within this block
     h = h0;
-    if (++mi < nm) {
-      qoff += (int64_t)(kRows * h_q - back) * D;
-      soff -= (int64_t)back * nblk * kAugEl - kAugEl;
-      return;
-    }
+    if (++mi < nm) return;
     ++t;
     valid = seek();
   }
@@ -436,18 +451,15 @@ struct StepIter {
   __device__ int lo() const { return mi == 0 ? lo0 : 0; }
   __device__ int hi() const { return mi == nm - 1 ? hin : kRows; }
   __device__ int qb() const { return qb0 + kRows * mi; }        // q_loc of the block's row 0
-  __device__ bool clamp() const { return clamp_last && mi == nm - 1; }
-  __device__ int64_t m0() const { return row0 + (int64_t)kRows * mi; }
 };
 
 template <int D>
 __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_bwd_dkdv_kernel(
-    const f16 *__restrict__ k, const f16 *__restrict__ v, const f16 *__restrict__ q,
-    const f16 *__restrict__ dout, const f16 *__restrict__ aug,
+    const f16 *__restrict__ k, const f16 *__restrict__ v, const f16 *__restrict__ rec,
     const int64_t *__restrict__ cu, const libra_tile_t *__restrict__ tiles, int64_t T,
     const BwdItem *__restrict__ items, int32_t *__restrict__ hdr, int h_q, int h_kv,
-    int64_t n_q, int64_t n_kv, int64_t nq_pad, float scale, float c2,
-    void *__restrict__ dk_out, void *__restrict__ dv_out, int accumulate) {
+    int64_t n_q, int64_t n_kv, float scale, float c2, void *__restrict__ dk_out,
+    void *__restrict__ dv_out, int accumulate) {
   using S = KvShape<D>;
   extern __shared__ __attribute__((aligned(16))) bf16 smem[];
   __shared__ int32_t s_item;
@@ -455,34 +467,23 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
   const int tid = threadIdx.x, l = tid & 63, ln = l & 31, kg = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index (uniform)
   const int G = h_q / h_kv;
-  const int64_t nblk = nq_pad / kRows;
   const int q_serve = xcd_of_workgroup();
   int q_state = kTakeFirst;
   // per-lane LDS offsets (elements) of the operand reads: rows of Q / dO for
-  // S and dP (row perm32(ln), 8 columns), and the transpose reads that give
-  // dO^T / Q^T for dV^T and dK^T: this lane addresses 4 columns of row
-  // 8 kg + 4 half + i of the block (i = (l % 16) / 4), the columns whose
-  // 16-lane group hands them to the lanes that need column perm32(ln)
+  // S and dP (row perm32(ln), chunk 2 c + kg; one offset per parity of c), and
+  // the transpose reads that give dO^T / Q^T for dV^T and dK^T: this lane
+  // addresses 4 columns of row 8 kg + 4 half + i of the block (i = (l % 16) /
+  // 4), the columns whose 16-lane group hands them to the lanes that need
+  // column perm32(ln) (one offset per half)
   const int prow = perm32(ln);
-  int qoff[D / 16], troff[D / 32][2];
-  static_for<D / 16>([&](auto c) { qoff[c] = prow * D + 8 * swt<S::QC>(prow, 2 * c + kg); });
+  const int qoff[2] = {rec_at(prow, kg), rec_at(prow, 2 + kg)};
+  int troff[2];
   {
     const int grp = l >> 4, i = (l & 15) >> 2, r = l & 3;
-    static_for<D / 32>([&](auto dt) {
-      static_for<2>([&](auto hf) {
-        const int row = 8 * (grp >> 1) + 4 * hf + i;
-        const int chunk = 4 * dt + 2 * (grp & 1) + (r & 1);
-        troff[dt][hf] = row * D + 8 * swt<S::QC>(row, chunk) + 4 * (r >> 1);
-      });
+    static_for<2>([&](auto hf) {
+      troff[hf] = rec_at(8 * (grp >> 1) + 4 * hf + i, 2 * (grp & 1) + (r & 1)) + 4 * (r >> 1);
     });
   }
-  // per-lane parts of the staging addresses (bytes), fixed for the kernel
-  static_assert(S::NQ == 1 || S::NQ == 2, "two or four staging copies per head");
-  uint32_t q_lane[S::NQ];
-  static_for<S::NQ>([&](auto u) {
-    const int r = (w + kWaves * u) * (64 / S::QC) + l / S::QC;
-    q_lane[u] = 2u * (uint32_t)(r * h_q * D + 8 * swt<S::QC>(r, l % S::QC));
-  });
   // B operand of the augmented k-block: ones in k = 0, 1, 2 (lanes of kg 0)
   f16x8 ones3;
   static_for<8>([&](auto i) { ones3[int(i)] = f16(kg == 0 && i < 3 ? 1.f : 0.f); });
@@ -490,6 +491,7 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
   // scores come out multiplied by s_q s_k, dP and D by s_o s_v, so the
   // exponent takes c2 / (s_q s_k) and the outputs are scaled back at the end
   // (exactly: all factors are powers of two).
+  const bool odd_heads = hdr[kOddHeads] != 0;
   const float s_q = fp16_scale((uint32_t)hdr[kMaxAbs + 0], false);
   const float s_o = fp16_scale((uint32_t)hdr[kMaxAbs + 1], true);
   const float s_k = fp16_scale((uint32_t)hdr[kMaxAbs + 2], false);
@@ -533,70 +535,51 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
       dka[dt] = mfma_zero();
     });
 
-    // ---- one step = (32-row query block, head); its Q, dO rows and aug go
-    // global -> LDS into ring stage `sg` (rows of the block outside the
-    // fragment are real rows of other fragments or the clamped last row;
-    // their P and dS are masked to zero)
-    auto issue = [&](const StepIter &st, int sg) {
-      // head h into the first half of the stage, head h + 1 (or h again when
-      // the step has one head; it is then not computed) into the second
-      const int64_t dq2 = st.two() ? D : 0, ds2 = st.two() ? nblk * kAugEl : 0;
-      static_for<2>([&](auto hb) {
-        bf16 *Qs = smem + sg * S::STAGE_EL + hb * S::HEAD_EL;
-        bf16 *dOs = Qs + S::Q_EL;
-        const int64_t qo = st.qoff + (hb ? dq2 : 0);
-        if (!st.clamp()) {
-          // wave w stages rows w * 64 / QC ... of each 16-byte column group;
-          // wave loads u = 0, 1 land 1 KiB x (w + 4 u) into the tile
-          const uint32_t lq = lds_addr(Qs) + 1024u * w, ld = lds_addr(dOs) + 1024u * w;
-          if constexpr (S::NQ == 2)
-            g2l16x4(q + qo, dout + qo, q_lane[0], q_lane[1], lq, lq + 4096u, ld, ld + 4096u);
-          else
-            g2l16x2(q + qo, dout + qo, q_lane[0], lq, ld);
-        } else {
-          // the last block of the buffer: rows past it read the last row (masked)
-          const int64_t m0 = st.m0();
-          const int hh = st.h + (hb && st.two() ? 1 : 0);
-          static_for<S::NQ>([&](auto u) {
-            const int wl = w + kWaves * u;
-            const int r = wl * (64 / S::QC) + l / S::QC;
-            const int64_t row = m0 + r < n_q ? m0 + r : n_q - 1;
-            const size_t off = ((size_t)row * h_q + hh) * D + 8 * swt<S::QC>(r, l % S::QC);
-            g2l16(q + off, Qs + wl * 512);
-            g2l16(dout + off, dOs + wl * 512);
-          });
-        }
-      });
-      // one augmented record per wave: head w / 2, record w % 2
-      const int64_t ao = st.soff + (w >= 2 ? ds2 : 0) + (w & 1) * (kAugEl / 2);
-      g2l16s(aug + ao, 16u * l,
-             lds_addr(smem + sg * S::STAGE_EL + (w >> 1) * S::HEAD_EL + 2 * S::Q_EL +
-                      (w & 1) * (kAugEl / 2)));
+    // ---- one step = (32-row query block, two heads): the records of heads h
+    // and h + 1, contiguous, go global -> LDS into ring stage `sg`, a quarter
+    // by each wave (a step of one head copies the record after its own too:
+    // not computed; rows of the block outside the fragment are rows of other
+    // fragments or zeros, their P and dS are masked to zero)
+    const char *cp_src = nullptr;   // the step being copied
+    uint32_t cp_dst = 0;
+    auto copy_part = [&](auto part) {
+      constexpr int at = S::LOADS * part / 3, n = S::LOADS * (part + 1) / 3 - at;
+      g2l_run<n>(cp_src + 1024 * at, 16u * l, cp_dst + 1024u * at);
     };
+    auto copy_all = [&]() { static_for<3>([&](auto part) { copy_part(part); }); };
 
     // ---- compute one step from the LDS stage at Qs.  Rows of the block are
     // m0 + iq, iq in [0, 32); with MASK, row iq counts for this lane's key
     // only when lower <= iq < upper (inside the fragment and causal).
-    auto step = [&](bool full, const bf16 *Qs, int lower, int upper) {
+    auto step = [&](auto copy_t, bool full, const bf16 *Qs, int lower, int upper) {
+      constexpr bool COPY = decltype(copy_t)::value;   // posts the copies of the iteration
       constexpr int NC = D / 16, NT = D / 32;
-      const bf16 *dOs = Qs + S::Q_EL;
-      const bf16 *Ag = dOs + S::Q_EL;     // -LSE / scale record, then the -D record
+      const bf16 *Ag = Qs + 2 * S::Q_EL + 8 * l;   // -LSE / scale operand, then the -D operand
+      // Q rows, then (at Q_EL) dO rows; the transpose reads of Q^T, then dO^T
+      const bf16 *rp[2] = {Qs + qoff[0], Qs + qoff[1]};
+      const f16 *tp[2] = {reinterpret_cast<const f16 *>(Qs) + troff[0],
+                          reinterpret_cast<const f16 *>(Qs) + troff[1]};
       // (1) Q rows and this lane's part of the -LSE / scale operand
       f16x8 qa[NC], oa[NC], sag, dag;
-      sag = *reinterpret_cast<const f16x8 *>(Ag + 8 * l);
-      static_for<NC>([&](auto c) { qa[c] = *reinterpret_cast<const f16x8 *>(Qs + qoff[c]); });
+      sag = *reinterpret_cast<const f16x8 *>(Ag);
+      static_for<NC>([&](auto c) {
+        qa[c] = *reinterpret_cast<const f16x8 *>(rp[c & 1] + 1024 * (c >> 1));
+      });
       __builtin_amdgcn_sched_barrier(0);
       // (2) S - LSE / scale = [Q | aug] [K | ones]^T (queries on M, this
       // lane's key on N) while the dO rows and the -D operand load
       f32x16 sa = mfma32h(sag, ones3, mfma_zero_c()), pa;
       static_for<NC>([&](auto c) { sa = mfma32h(qa[c], kf[c], sa); });
-      dag = *reinterpret_cast<const f16x8 *>(Ag + kAugEl / 2 + 8 * l);
-      static_for<NC>([&](auto c) { oa[c] = *reinterpret_cast<const f16x8 *>(dOs + qoff[c]); });
+      dag = *reinterpret_cast<const f16x8 *>(Ag + kAugEl / 2);
+      static_for<NC>([&](auto c) {
+        oa[c] = *reinterpret_cast<const f16x8 *>(rp[c & 1] + S::Q_EL + 1024 * (c >> 1));
+      });
       static_for<NC + 1>([&](auto i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, i < NC / 2 + 1 ? 2 : 0, 0);
       });
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (COPY) copy_part(std::integral_constant<int, 0>{});
       // (3) dP - D = [dO | aug] [V | ones]^T with P = exp2((S - LSE / scale) c2)
       // on the VALU and the transpose reads of dO^T; register 8 hh + i of S
       // holds row 16 hh + 8 kg + i
@@ -621,8 +604,8 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
       });
       static_for<NT>([&](auto dt) {
         static_for<2>([&](auto c) {
-          const f16 *base = reinterpret_cast<const f16 *>(dOs) + 16 * c * D;
-          ta[dt][c] = lds_tr16x2h(base + troff[dt][0], base + troff[dt][1]);
+          constexpr int at = S::Q_EL + 128 * c + 1024 * dt;
+          ta[dt][c] = lds_tr16x2h(tp[0] + at, tp[1] + at);
         });
       });
       static_for<NC + 1>([&](auto i) {
@@ -634,6 +617,7 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
       if (full) phase3(std::false_type{});
       else phase3(std::true_type{});
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (COPY) copy_part(std::integral_constant<int, 1>{});
       // (4) dV^T += dO^T P with dS = P (dP - D) on the VALU and the transpose
       // reads of Q^T
       f16x8 tq[NT][2];
@@ -648,8 +632,8 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
       });
       static_for<NT>([&](auto dt) {
         static_for<2>([&](auto c) {
-          const f16 *base = reinterpret_cast<const f16 *>(Qs) + 16 * c * D;
-          tq[dt][c] = lds_tr16x2h(base + troff[dt][0], base + troff[dt][1]);
+          constexpr int at = 128 * c + 1024 * dt;
+          tq[dt][c] = lds_tr16x2h(tp[0] + at, tp[1] + at);
         });
       });
       static_for<2 * NT>([&](auto i) {
@@ -658,22 +642,141 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
       });
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (COPY) copy_part(std::integral_constant<int, 2>{});
       // (5) dK^T += Q^T dS
       static_for<NT>([&](auto dt) {
         static_for<2>([&](auto c) { dka[dt] = mfma32h(tq[dt][c], db16[c], dka[dt]); });
       });
     };
 
+    // ---- compute a step of two heads: the products of one head run while the
+    // VALU works on the other's scores, so that no product waits for them and
+    // the matrix cores always have one queued.  Phases of NC + 1 or 2 NT
+    // products each: S of head 0, S of head 1 (exp of head 0), dP of 0 (exp of
+    // 1), dP of 1 (dS of 0), dV of 0 (dS of 1), dK of 0, dV of 1, dK of 1.  Each
+    // operand is read AH products before the one that takes it, also across
+    // phases.  Masks as in step().
+    auto step2 = [&](bool full, const bf16 *Qs, int lower, int upper) {
+      constexpr int NC = D / 16, NT = D / 32, AH = 4;
+      constexpr int N1 = NC + 1, N2 = 2 * NT;   // products of an S / dP, a dV / dK phase
+      constexpr int NOPS = 4 * N1 + 4 * N2;
+      const bf16 *Ag = Qs + 2 * S::Q_EL + 8 * l;
+      const bf16 *rp[2] = {Qs + qoff[0], Qs + qoff[1]};
+      const f16 *tp[2] = {reinterpret_cast<const f16 *>(Qs) + troff[0],
+                          reinterpret_cast<const f16 *>(Qs) + troff[1]};
+      f32x16 sa[2], pa[2];        // S - LSE / scale, then P; dP - D
+      f16x8 p16[2][2], s16[2][2];  // P and dS as operands
+      f16x8 op[NOPS];
+      // phase and product of operation n
+      auto rd = [&](auto n_t) {
+        constexpr int n = decltype(n_t)::value;
+        if constexpr (n < 4 * N1) {
+          constexpr int ph = n / N1, i = n % N1, hb = ph & 1, which = ph / 2;   // Q, then dO
+          if constexpr (i == 0)
+            op[n] = *reinterpret_cast<const f16x8 *>(Ag + hb * S::HEAD_EL + which * (kAugEl / 2));
+          else
+            op[n] = *reinterpret_cast<const f16x8 *>(rp[(i - 1) & 1] + hb * S::HEAD_EL +
+                                                    which * S::Q_EL + 1024 * ((i - 1) >> 1));
+        } else if constexpr (n < NOPS) {
+          constexpr int m = n - 4 * N1, ph = m / N2, j = m % N2, hb = ph / 2;
+          constexpr int dt = j >> 1, c = j & 1;
+          constexpr int at = hb * S::HEAD_EL + (ph & 1 ? 0 : S::Q_EL) + 128 * c + 1024 * dt;
+          op[n] = lds_tr16x2h(tp[0] + at, tp[1] + at);   // dO^T, then Q^T
+        }
+      };
+      // VALU elements of head hb: P = exp2((S - LSE / scale) c2) and its rounding;
+      // dS = P (dP - D) and its rounding.  Register 8 hh + i is row 16 hh + 8 kg + i
+      auto exp_el = [&](auto hb, auto r_t) {
+        constexpr int r = decltype(r_t)::value;
+        float p = fast_exp2(sa[hb][r] * c2s);
+        asm volatile("" : "+v"(p));   // stays in its slot
+        sa[hb][r] = p;
+      };
+      auto mask = [&](auto hb) {
+        int lo = lower - 8 * kg, hi = upper - 8 * kg;
+        asm volatile("" : "+v"(lo), "+v"(hi));   // the comparisons stay in this branch
+        static_for<16>([&](auto r) {
+          constexpr int iq = 16 * (r >> 3) + (r & 7);
+          sa[hb][int(r)] = (iq >= lo && iq < hi) ? sa[hb][int(r)] : -INFINITY;
+        });
+      };
+      auto p_round = [&](auto hb, auto r_t) {
+        constexpr int r = decltype(r_t)::value;
+        p16[hb][r >> 3][r & 7] = static_cast<f16>(sa[hb][r]);
+      };
+      auto ds_el = [&](auto hb, auto r_t) {
+        constexpr int r = decltype(r_t)::value;
+        s16[hb][r >> 3][r & 7] = static_cast<f16>(sa[hb][r] * pa[hb][r]);
+      };
+      // 16 elements over the slots [2, n) of a phase of n products
+      auto spread = [&](auto i_t, auto n_t, auto &&f) {
+        constexpr int i = decltype(i_t)::value, n = decltype(n_t)::value;
+        if constexpr (i >= 2) {
+          constexpr int a = 16 * (i - 2) / (n - 2), b = 16 * (i - 1) / (n - 2);
+          static_for<b - a>([&](auto e) { f(std::integral_constant<int, a + e>{}); });
+        }
+      };
+      using H0 = std::integral_constant<int, 0>;
+      using H1 = std::integral_constant<int, 1>;
+      using L1 = std::integral_constant<int, N1>;
+      using L2 = std::integral_constant<int, N2>;
+      static_for<AH>([&](auto n) { rd(n); });
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<4>([&](auto ph) {
+        static_for<N1>([&](auto i) {
+          constexpr int n = ph * N1 + i, hb = ph & 1;
+          f32x16 &acc = ph < 2 ? sa[hb] : pa[hb];
+          if constexpr (i == 0) acc = mfma32h(op[n], ones3, mfma_zero_c());
+          else acc = mfma32h(op[n], ph < 2 ? kf[i > 0 ? i - 1 : 0] : vf[i > 0 ? i - 1 : 0], acc);
+          rd(std::integral_constant<int, n + AH>{});
+          if constexpr (ph == 1) spread(i, L1{}, [&](auto r) { exp_el(H0{}, r); });
+          if constexpr (ph == 2) {
+            if constexpr (i < 2)
+              static_for<8>([&](auto e) { p_round(H0{}, std::integral_constant<int, 8 * i + e>{}); });
+            spread(i, L1{}, [&](auto r) { exp_el(H1{}, r); });
+          }
+          if constexpr (ph == 3) {
+            if constexpr (i < 2)
+              static_for<8>([&](auto e) { p_round(H1{}, std::integral_constant<int, 8 * i + e>{}); });
+            spread(i, L1{}, [&](auto r) { ds_el(H0{}, r); });
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (ph < 2)
+          if (!full) mask(ph);
+        if constexpr (ph == 1) copy_part(std::integral_constant<int, 0>{});
+        if constexpr (ph == 3) copy_part(std::integral_constant<int, 1>{});
+      });
+      static_for<4>([&](auto ph) {
+        static_for<N2>([&](auto j) {
+          constexpr int n = 4 * N1 + ph * N2 + j, hb = ph / 2, dt = j >> 1, c = j & 1;
+          if constexpr (ph & 1) dka[dt] = mfma32h(op[n], s16[hb][c], dka[dt]);
+          else dva[dt] = mfma32h(op[n], p16[hb][c], dva[dt]);
+          rd(std::integral_constant<int, n + AH>{});
+          if constexpr (ph == 0) spread(j, L2{}, [&](auto r) { ds_el(H1{}, r); });
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (ph == 1) copy_part(std::integral_constant<int, 2>{});
+      });
+    };
+
     // Steps are walked once, at issue; what the compute side needs of the step
     // in ring stage j (lo | hi << 8 | two << 16, and the q_loc of the block's
     // row 0) waits in lane j of desc / desc_qb.
-    StepIter iss{tiles, T, n_q, n_kv, key0, len, h_q, g, G, kloc0, D, nblk};
+    StepIter iss{tiles, T, n_q, n_kv, key0, len, h_q, g, G, kloc0,
+                 2 * S::HEAD_EL};
     iss.start();
     int desc = 0, desc_qb = 0;
     int issued = 0, computed = 0;
-    auto issue_next = [&]() {
-      const int sg = issued & (S::NSTAGE - 1);
-      issue(iss, sg);
+    // ring stage and descriptor of the next step to copy; after the last one,
+    // its copies are repeated into the free stages, so that every iteration
+    // posts as many and no product phase branches on it
+    auto next_step = [&](int posted) {
+      constexpr uint32_t bytes = 2u * S::STAGE_EL / kWaves;
+      const int sg = posted & (S::NSTAGE - 1);
+      cp_dst = lds_addr(smem + sg * S::STAGE_EL) + bytes * w;
+      if (!iss.valid) return;
+      cp_src = reinterpret_cast<const char *>(rec) + uniform64(iss.rec) + bytes * w;
       if (l == sg) {
         desc = iss.lo() | iss.hi() << 8 | (iss.two() ? 1 << 16 : 0);
         desc_qb = iss.qb();
@@ -681,38 +784,54 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
       iss.next();
       ++issued;
     };
-    while (iss.valid && issued < S::NSTAGE - 1) issue_next();
-    // of the eight places modulo 32 bytes this one was the best: 100.1 ms on the
-    // 256K share against 100.8 to 102.7
-    align_code<1>();
-    while (computed < issued) {
-      // keep up to NSTAGE - 1 steps in flight, the one computed now included
-      if (iss.valid && issued < computed + S::NSTAGE - 1) issue_next();
-      // wait for this step's loads: in steady state NSTAGE - 2 later steps
-      // stay in flight; near the end of an item, wait for everything
-      if (issued - 1 - computed >= S::NSTAGE - 2) {
+    if (iss.valid) {
+      for (int i = 0; i < S::NSTAGE - 1; ++i) {
+        next_step(i);
+        copy_all();
+      }
+    }
+    // one step per iteration; the loop of items whose every step has two heads
+    // is one of its own (accumulators that merge from two bodies in each
+    // iteration cost copies)
+    auto steps = [&](auto pairs_t) {
+      while (computed < issued) {
+        // this step's copies are in; the two later steps' stay in flight
         wait_vm_n<(S::NSTAGE - 2) * S::LOADS>();
-      } else {
-        wait_vm_n<0>();
-      }
-      barrier_nofence();
+        barrier_nofence();
+        // every wave is past the step before: the next one goes into its stage
+        next_step(computed + S::NSTAGE - 1);
 
-      const int sg = computed & (S::NSTAGE - 1);
-      const int dsc = __builtin_amdgcn_readlane(desc, sg);
-      const int lo_l = dsc & 0xff, hi_l = (dsc >> 8) & 0xff;
-      const bool two = (dsc >> 16) != 0;
-      const int qb = __builtin_amdgcn_readlane(desc_qb, sg);   // q_loc of the block's row 0
-      if (kw0 <= qb + hi_l - 1) {
-        const bf16 *Qs = smem + sg * S::STAGE_EL;
-        // interior blocks: every row inside the fragment and at or after every key
-        const bool full = lo_l == 0 && hi_l == kRows && wave_keys_ok && kw0 + 31 <= qb;
-        const int need = kl - qb;                               // first iq with q_loc >= kl
-        const int lower = need > lo_l ? (need < kRows ? need : kRows) : lo_l;
-        const int upper = key_ok ? hi_l : 0;
-        step(full, Qs, lower, upper);
-        if (two) step(full, Qs + S::HEAD_EL, lower, upper);
+        const int sg = computed & (S::NSTAGE - 1);
+        const int dsc = __builtin_amdgcn_readlane(desc, sg);
+        const int lo_l = dsc & 0xff, hi_l = (dsc >> 8) & 0xff;
+        const bool two = (dsc >> 16) != 0;
+        const int qb = __builtin_amdgcn_readlane(desc_qb, sg);   // q_loc of the block's row 0
+        if (kw0 <= qb + hi_l - 1) {
+          const bf16 *Qs = smem + sg * S::STAGE_EL;
+          // interior blocks: every row inside the fragment and at or after every key
+          const bool full = lo_l == 0 && hi_l == kRows && wave_keys_ok && kw0 + 31 <= qb;
+          const int need = kl - qb;                               // first iq with q_loc >= kl
+          const int lower = need > lo_l ? (need < kRows ? need : kRows) : lo_l;
+          const int upper = key_ok ? hi_l : 0;
+          if constexpr (decltype(pairs_t)::value) {
+            step2(full, Qs, lower, upper);
+          } else {
+            step(std::true_type{}, full, Qs, lower, upper);
+            if (two) step(std::false_type{}, full, Qs + S::HEAD_EL, lower, upper);
+          }
+        } else {
+          copy_all();
+        }
+        ++computed;
       }
-      ++computed;
+    };
+    if (odd_heads) {
+      steps(std::false_type{});
+    } else {
+      // of four places modulo 32 bytes the best: 91.9 ms on the 256K share
+      // against 92.5 to 92.6
+      align_code<5>();
+      steps(std::true_type{});
     }
 
     // ---- write dK, dV for this wave's 32 keys
@@ -764,13 +883,12 @@ BwdLayout bwd_layout(int64_t T, int64_t n, int64_t n_q, int64_t n_kv, int h_q, i
   L.gmask = align256b(L.ext + (size_t)n * sizeof(int32_t));
   L.items = align256b(L.gmask + (size_t)n * sizeof(unsigned long long));
   L.qitems = align256b(L.items + (size_t)L.max_items * sizeof(BwdItem));
-  L.q16 = align256b(L.qitems + (size_t)L.max_qitems * sizeof(FwdItem));
-  L.do16 = align256b(L.q16 + (size_t)n_q * h_q * d * sizeof(f16));
-  L.k16 = align256b(L.do16 + (size_t)n_q * h_q * d * sizeof(f16));
+  L.rec = align256b(L.qitems + (size_t)L.max_qitems * sizeof(FwdItem));
+  // one record more: a step of one head copies the record after its own
+  L.k16 = align256b(L.rec + (size_t)(L.nq_pad / kRows * h_q + 1) * rec_els(d) * sizeof(f16));
   L.v16 = align256b(L.k16 + (size_t)n_kv * h_kv * d * sizeof(f16));
   L.stats = align256b(L.v16 + (size_t)n_kv * h_kv * d * sizeof(f16));
-  L.aug = align256b(L.stats + (size_t)h_q * L.nq_pad * 2 * sizeof(float));
-  L.splits = align256b(L.aug + (size_t)h_q * (L.nq_pad / kRows) * kAugEl * sizeof(f16));
+  L.splits = align256b(L.stats + (size_t)h_q * L.nq_pad * 2 * sizeof(float));
   L.max_parts = kFwdSplitSlots;
   L.parts = align256b(L.splits + (size_t)(L.max_parts / 2) * sizeof(FwdSplit));
   L.total = align256b(L.parts + (size_t)L.max_parts * fwd_part_floats(d) * sizeof(float));
@@ -789,12 +907,10 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
   auto *gmask = reinterpret_cast<unsigned long long *>(ws + L.gmask);
   BwdItem *items = reinterpret_cast<BwdItem *>(ws + L.items);
   FwdItem *qitems = reinterpret_cast<FwdItem *>(ws + L.qitems);
-  f16 *q16 = reinterpret_cast<f16 *>(ws + L.q16);
-  f16 *do16 = reinterpret_cast<f16 *>(ws + L.do16);
+  f16 *rec = reinterpret_cast<f16 *>(ws + L.rec);
   f16 *k16 = reinterpret_cast<f16 *>(ws + L.k16);
   f16 *v16 = reinterpret_cast<f16 *>(ws + L.v16);
   float *stats = reinterpret_cast<float *>(ws + L.stats);
-  f16 *aug = reinterpret_cast<f16 *>(ws + L.aug);
   static bool attr_set = false;
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bwd_dkdv_kernel<D>),
@@ -821,31 +937,23 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
     float *parts = reinterpret_cast<float *>(ws + L.parts);
     enqueue_fwd_items(cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, qitems, L.max_qitems, false,
                       cus, L.max_parts, splits, st);
-    {
-      // stats and aug of rows outside the covered ones stay zero (finite):
-      // they are only read for masked rows; lanes 32..63 of aug stay zero
-      const int64_t s16 = (int64_t)(L.splits - L.stats) / 16;
-      hipLaunchKernelGGL(zero_kernel, dim3((unsigned)std::min<int64_t>((s16 + 255) / 256, 4096)),
-                         dim3(256), 0, st, reinterpret_cast<uint4 *>(stats), s16);
-    }
     hipLaunchKernelGGL(bwd_absmax_q_kernel<D>, dim3((unsigned)(T * kTileSplit)), dim3(256), 0, st,
-                       q, dout, tiles, h_q, n_q, n_kv, hdr, q16, do16);
+                       q, dout, tiles, h_q, n_q, n_kv, hdr, rec);
     hipLaunchKernelGGL((bwd_kv_pass_kernel<D, false>), dim3((unsigned)cus * 8), dim3(256), 0, st,
                        k, v, cu, n, ext, h_kv, n_kv, hdr, k16, v16);
     hipLaunchKernelGGL((bwd_kv_pass_kernel<D, true>), dim3((unsigned)cus * 8), dim3(256), 0, st,
                        k, v, cu, n, ext, h_kv, n_kv, hdr, k16, v16);
     hipLaunchKernelGGL(bwd_pre_kernel<D>, dim3((unsigned)(T * kTileSplit)), dim3(256), 0, st, q,
-                       o, dout, lse, tiles, h_q, n_q, n_kv, L.nq_pad, scale, hdr, q16, do16,
-                       stats, aug);
+                       o, dout, lse, tiles, h_q, n_q, n_kv, L.nq_pad, scale, hdr, rec, stats);
     // dQ first: it writes the -D records the dK / dV kernel reads
     const int rc = launch_bwd_dq(D, q, dout, k, v, stats, cu, qitems, hdr, h_q, h_kv, n_q, n_kv,
-                                 L.nq_pad, scale, dq, aug, splits, parts, L.max_parts, cus,
+                                 L.nq_pad, scale, dq, rec, splits, parts, L.max_parts, cus,
                                  st, tm_q);
     if (rc != LIBRA_OK) return rc;
     if (tm_kv) hipEventRecord(tm_kv->begin, st);
     hipLaunchKernelGGL(attn_bwd_dkdv_kernel<D>, dim3(cus), dim3(kThreads), KvShape<D>::SMEM, st,
-                       k16, v16, q16, do16, aug, cu, tiles, T, items, hdr, h_q, h_kv, n_q, n_kv,
-                       L.nq_pad, scale, scale * kLog2e, dk, dv, accumulate ? 1 : 0);
+                       k16, v16, rec, cu, tiles, T, items, hdr, h_q, h_kv, n_q, n_kv, scale,
+                       scale * kLog2e, dk, dv, accumulate ? 1 : 0);
     if (tm_kv) hipEventRecord(tm_kv->end, st);
   }
   const hipError_t e = hipGetLastError();

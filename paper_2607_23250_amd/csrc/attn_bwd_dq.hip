@@ -51,7 +51,7 @@ __global__ __launch_bounds__(2 * kThreads, 1) void attn_bwd_dq_kernel(
     const bf16 *__restrict__ v, const float *__restrict__ stats,
     const int64_t *__restrict__ cu, const FwdItem *__restrict__ items,
     int32_t *__restrict__ hdr, int h_q, int h_kv, int64_t n_q, int64_t n_kv, int64_t nq_pad,
-    float c2, float scale, bf16 *__restrict__ dq, f16 *__restrict__ aug,
+    float c2, float scale, bf16 *__restrict__ dq, f16 *__restrict__ rec,
     float *__restrict__ parts) {
   using S = DqShape<D>;
   extern __shared__ __attribute__((aligned(16))) bf16 smem[];
@@ -335,11 +335,10 @@ __global__ __launch_bounds__(2 * kThreads, 1) void attn_bwd_dq_kernel(
         // D_exact = D + sum_k dS_k (sum_k P_k = 1): the -D record of the dK / dV
         // kernel's augmented operands for this (row, head)
         if (kg == 0) {
-          f16x8 rec;
-          split3h(-d_exact * s_ov, rec);
-          *reinterpret_cast<f16x8 *>(aug + ((size_t)head * (nq_pad / kRows) + row / kRows) *
-                                               kAugEl +
-                                     kAugEl / 2 + 8 * perm32((int)(row % kRows))) = rec;
+          f16x8 dv;
+          split3h(-d_exact * s_ov, dv);
+          *reinterpret_cast<f16x8 *>(rec + ((size_t)(row / kRows) * h_q + head + 1) * rec_els(D) -
+                                     kAugEl / 2 + 8 * perm32((int)(row % kRows))) = dv;
         }
       }
     }
@@ -355,7 +354,7 @@ template <int D>
 __global__ __launch_bounds__(256) void bwd_dq_combine_kernel(
     const FwdSplit *__restrict__ splits, const int32_t *__restrict__ hdr,
     const float *__restrict__ parts, const float *__restrict__ stats, int h_q, int64_t nq_pad,
-    float scale, bf16 *__restrict__ dq, f16 *__restrict__ aug) {
+    float scale, bf16 *__restrict__ dq, f16 *__restrict__ rec) {
   constexpr size_t PF = fwd_part_floats(D);
   const int count = hdr[kFwdSplits];
   const float s_ov = fp16_scale((uint32_t)hdr[kMaxAbs + 1], true) *
@@ -375,9 +374,9 @@ __global__ __launch_bounds__(256) void bwd_dq_combine_kernel(
     for (int i = 0; i < D / 2; ++i) acc[i] = 0.f;
     float dsum = 0.f;
     for (int p = 0; p < sp.parts; ++p) {
-      const float *rec = parts + (size_t)(sp.base + p) * PF;
-      dsum += rec[(size_t)kFwdPartRows * D + pr];
-      const float4 *src = reinterpret_cast<const float4 *>(rec + (size_t)pr * D + half * (D / 2));
+      const float *pt = parts + (size_t)(sp.base + p) * PF;
+      dsum += pt[(size_t)kFwdPartRows * D + pr];
+      const float4 *src = reinterpret_cast<const float4 *>(pt + (size_t)pr * D + half * (D / 2));
 #pragma unroll
       for (int i = 0; i < D / 8; ++i) {
         const float4 x = src[i];
@@ -398,10 +397,10 @@ __global__ __launch_bounds__(256) void bwd_dq_combine_kernel(
     if (half == 0) {
       const size_t blk = (size_t)head * (nq_pad / kRows) + row / kRows;
       const float d_exact = stats[blk * 2 * kRows + kRows + row % kRows] + dsum;
-      f16x8 rec;
-      split3h(-d_exact * s_ov, rec);
-      *reinterpret_cast<f16x8 *>(aug + blk * kAugEl + kAugEl / 2 + 8 * perm32((int)(row % kRows))) =
-          rec;
+      f16x8 dv;
+      split3h(-d_exact * s_ov, dv);
+      *reinterpret_cast<f16x8 *>(rec + ((size_t)(row / kRows) * h_q + head + 1) * rec_els(D) -
+                                 kAugEl / 2 + 8 * perm32((int)(row % kRows))) = dv;
     }
   }
 }
@@ -409,7 +408,7 @@ __global__ __launch_bounds__(256) void bwd_dq_combine_kernel(
 int launch_bwd_dq(int d, const bf16 *q, const bf16 *dout, const bf16 *k, const bf16 *v,
                   const float *stats, const int64_t *cu, const FwdItem *items, int32_t *hdr,
                   int h_q, int h_kv, int64_t n_q, int64_t n_kv, int64_t nq_pad, float scale,
-                  bf16 *dq, f16 *aug, const FwdSplit *splits, float *parts, int max_parts,
+                  bf16 *dq, f16 *rec, const FwdSplit *splits, float *parts, int max_parts,
                   int blocks, hipStream_t st, const KernelTimer *tm) {
   static bool attr_set[2] = {false, false};
   const int which = d == 128 ? 1 : 0;
@@ -426,17 +425,17 @@ int launch_bwd_dq(int d, const bf16 *q, const bf16 *dout, const bf16 *k, const b
   if (d == 128) {
     hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, dim3(blocks), dim3(2 * kThreads), smem, st, q, dout,
                        k, v, stats, cu, items, hdr, h_q, h_kv, n_q, n_kv, nq_pad, scale * kLog2e,
-                       scale, dq, aug, parts);
+                       scale, dq, rec, parts);
     if (max_parts > 0)
       hipLaunchKernelGGL(bwd_dq_combine_kernel<128>, dim3(blocks), dim3(256), 0, st, splits, hdr,
-                         parts, stats, h_q, nq_pad, scale, dq, aug);
+                         parts, stats, h_q, nq_pad, scale, dq, rec);
   } else {
     hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, dim3(blocks), dim3(2 * kThreads), smem, st, q, dout,
                        k, v, stats, cu, items, hdr, h_q, h_kv, n_q, n_kv, nq_pad, scale * kLog2e,
-                       scale, dq, aug, parts);
+                       scale, dq, rec, parts);
     if (max_parts > 0)
       hipLaunchKernelGGL(bwd_dq_combine_kernel<64>, dim3(blocks), dim3(256), 0, st, splits, hdr,
-                         parts, stats, h_q, nq_pad, scale, dq, aug);
+                         parts, stats, h_q, nq_pad, scale, dq, rec);
   }
   if (tm) hipEventRecord(tm->end, st);
   return LIBRA_OK;

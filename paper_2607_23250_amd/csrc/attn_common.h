@@ -44,6 +44,7 @@ constexpr int kPrepThreads = 1024;
 // starts at [base+16, base+24).
 enum HdrSlot {
   kBadTiles = 4,   // tiles skipped because they were out of range (+1 on item overflow)
+  kOddHeads = 5,   // backward: some tile covers an odd number of a KV group's heads
   kFwdQ = 8,       // forward / dQ work items
   kBwdQ = 32,      // dK/dV work items
   kMaxAbs = 56,    // backward: max |x| (fp32 bits) of Q, dO, K, V in slots 56..59
@@ -51,6 +52,21 @@ enum HdrSlot {
   kHdrSlots = 64
 };
 static_assert(kBadTiles * 4 == LIBRA_WS_SKIPPED_OFFSET, "documented offset of the skip count");
+
+// Compile-time loop: f(std::integral_constant<int, i>{}) for i in [0, N).  Register
+// arrays indexed this way are kept in registers (a runtime-indexed or
+// captured array can end up in scratch memory).
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for_impl(F &&f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for_impl<I + 1, N>(f);
+  }
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+  static_for_impl<0, N>(f);
+}
 
 // Cost bucket, 0 = longest: exact below 512, then 32 units per bucket.
 __device__ __forceinline__ int cost_bucket(int64_t c) {
@@ -246,9 +262,22 @@ __device__ __forceinline__ float row_sum2(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Backward "aug" records: per 32-row block and query head, two MFMA
-// A-operands of 64 lanes x 8 fp16 (-LSE / scale, then -D; see bwd_pre_kernel).
+// Backward records: all that a dK / dV step reads of one 32-row block of the
+// query rows and one query head, contiguous and already in the order of the
+// LDS stage: the scaled fp16 copies of Q and of dO (32 x D each, placed by
+// rec_at), then two MFMA A-operands of 64 lanes x 8 fp16 (-LSE / scale, then
+// -D; see bwd_pre_kernel).  Record (block m, head h) is number m * h_q + h.
 constexpr int kAugEl = 2 * 64 * 8;
+__host__ __device__ constexpr int rec_els(int d) { return 2 * kRows * d + kAugEl; }
+// Place (in elements) of 16-byte chunk `col` of row `row` in a record's Q or
+// dO part: chunk by chunk, 32 rows each, the rows of a chunk permuted so that
+// row reads (16 rows at one chunk) and transpose reads (4 rows x 4 chunks)
+// both touch every bank once.  Chunks 4 apart and rows 16 apart lie at fixed
+// distances: every operand read is one of two per-lane addresses plus an
+// immediate.
+__host__ __device__ __forceinline__ int rec_at(int row, int col) {
+  return 8 * kRows * col + 8 * (row ^ (4 * (col & 3)));
+}
 
 
 // Swizzle of row-major Q / dO / K / V tiles that are read both by rows
@@ -318,6 +347,14 @@ __device__ __forceinline__ f16x8 lds_tr16x2h(const f16 *p0, const f16 *p1) {
   const i16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
       (__attribute__((address_space(3))) i16x4 *)(p1));
   return __builtin_bit_cast(f16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// A value that is the same in every lane, as the compiler cannot see by itself
+// (64-bit products run on the VALU).
+__device__ __forceinline__ int64_t uniform64(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+  return (int64_t)((uint64_t)hi << 32 | lo);
 }
 
 // Asynchronous 16-byte global -> LDS copy by one wave: lane i's bytes land at
@@ -412,6 +449,31 @@ __device__ __forceinline__ void g2l16s(const void *g, uint32_t o, uint32_t la) {
       : "v"(o), "s"(la), "s"(g)
       : "memory");
 }
+// N <= 4 such copies, contiguous on both sides: lane bytes at g + o + 1024 i
+// land at la + 1024 i (the immediate offset counts on both sides).
+template <int N>
+__device__ __forceinline__ void g2l_run(const void *g, uint32_t o, uint32_t la) {
+  static_assert(N >= 1 && N <= 4, "the immediate offset reaches 4095 bytes");
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, %3\n\t"
+      ".if %4 > 1\n\t"
+      "global_load_lds_dwordx4 %1, %3 offset:1024\n\t"
+      ".endif\n\t"
+      ".if %4 > 2\n\t"
+      "global_load_lds_dwordx4 %1, %3 offset:2048\n\t"
+      ".endif\n\t"
+      ".if %4 > 3\n\t"
+      "global_load_lds_dwordx4 %1, %3 offset:3072\n\t"
+      ".endif\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "v"(o), "s"(la), "s"(g), "n"(N)
+      : "memory");
+}
 // Two such copies: the row at o0 from ga to la0 and from gb to lb0.
 __device__ __forceinline__ void g2l16x2(const void *ga, const void *gb, uint32_t o0,
                                         uint32_t la0, uint32_t lb0) {
@@ -465,21 +527,6 @@ __device__ __forceinline__ void sched_pipeline() {
     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // DS read
   }
   __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
-}
-
-// Compile-time loop: f(std::integral_constant<int, i>{}) for i in [0, N).  Register
-// arrays indexed this way are kept in registers (a runtime-indexed or
-// captured array can end up in scratch memory).
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for_impl(F &&f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for_impl<I + 1, N>(f);
-  }
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-  static_for_impl<0, N>(f);
 }
 
 // x as hi + mid + lo, three bf16 values in elements 0..2 of r, the rest zero
@@ -586,8 +633,8 @@ struct FwdLayout {
   int32_t max_parts = 0;   // 0: items are never split
 };
 struct BwdLayout {
-  size_t hdr = 0, ext = 0, gmask = 0, items = 0, qitems = 0, q16 = 0, do16 = 0, k16 = 0,
-         v16 = 0, stats = 0, aug = 0, splits = 0, parts = 0, total = 0;
+  size_t hdr = 0, ext = 0, gmask = 0, items = 0, qitems = 0, rec = 0, k16 = 0,
+         v16 = 0, stats = 0, splits = 0, parts = 0, total = 0;
   int32_t max_parts = 0;   // split-K partial slots of the dQ kernel
   int64_t max_items = 0, max_qitems = 0, nq_pad = 0;
 };
@@ -625,7 +672,7 @@ int launch_fwd(const void *q, const void *k, const void *v, const int64_t *cu, i
 int launch_bwd_dq(int d, const bf16 *q, const bf16 *dout, const bf16 *k, const bf16 *v,
                   const float *stats, const int64_t *cu, const FwdItem *items, int32_t *hdr,
                   int h_q, int h_kv, int64_t n_q, int64_t n_kv, int64_t nq_pad, float scale,
-                  bf16 *dq, f16 *aug, const FwdSplit *splits, float *parts, int max_parts,
+                  bf16 *dq, f16 *rec, const FwdSplit *splits, float *parts, int max_parts,
                   int blocks, hipStream_t st, const KernelTimer *tm);
 int launch_bwd(const void *q, const void *k, const void *v, const void *o, const float *lse,
                const void *dout, const int64_t *cu, int64_t n, const libra_tile_t *tiles,

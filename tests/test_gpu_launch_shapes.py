@@ -25,7 +25,7 @@ def _tiles(spans):
 
 
 def _check(lengths, tiles, h_q, h_kv, d, seed=5):
-    """fwd + accumulate-mode bwd of `tiles` (one head range over all rows)."""
+    """fwd + accumulate-mode bwd of `tiles` (which cover one range of heads on all rows)."""
     n = sum(lengths)
     q, k, v, do = wl.tensors(seed, n, n, h_q, h_kv, d)
     qd, kd, vd, dod = (t.to(DEV) for t in (q, k, v, do))
@@ -34,7 +34,7 @@ def _check(lengths, tiles, h_q, h_kv, d, seed=5):
     o, lse = pl.libra_attn_fwd(qd, kd, vd, cu, td)
     dq, dk, dv = pl.libra_attn_bwd(qd, kd, vd, o, lse, dod, cu, td, accumulate=True)
     torch.cuda.synchronize()
-    h0, h1 = int(tiles["head_begin"][0]), int(tiles["head_end"][0])
+    h0, h1 = int(tiles["head_begin"].min()), int(tiles["head_end"].max())
     g0, g1 = h0 * h_kv // h_q, (h1 - 1) * h_kv // h_q + 1
     G = h_q // h_kv
     assert h0 % G == 0 and h1 % G == 0, "whole KV groups"
@@ -62,3 +62,20 @@ def test_one_queue_holds_every_item(n_items):
     n = sum(lengths)
     say(f"[one queue] {n_items} items of one head, {n} rows")
     _check(lengths, _tiles([(0, n, 3, 4)]), 8, 8, 64)
+
+
+@pytest.mark.parametrize("d", (64, 128))
+@pytest.mark.parametrize("cuts", ((0, 4, 8), (0, 2, 4, 8), (0, 1, 4, 7, 8), (0, 3, 8)))
+def test_head_ranges_and_shared_row_blocks(cuts, d):
+    """Two KV heads of four query heads each, the heads cut into ranges of even
+    and odd widths (a dK / dV step takes two heads, or one) and the rows into
+    tiles that end inside 32-row blocks, differently for each range; samples of
+    1 to 300 rows, the last block of the buffer not full."""
+    lengths = [1, 300, 31, 33, 129, 64, 2, 95]
+    n = sum(lengths)
+    spans = []
+    for i, (a, b) in enumerate(zip(cuts[:-1], cuts[1:])):
+        rows = list(range(0, n, 37 + 11 * i)) + [n]
+        spans += [(x, y, a, b) for x, y in zip(rows[:-1], rows[1:])]
+    say(f"[head ranges] {cuts} d={d} rows={n} tiles={len(spans)}")
+    _check(lengths, _tiles(spans), 8, 2, d)
