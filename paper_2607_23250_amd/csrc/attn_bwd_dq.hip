@@ -349,36 +349,39 @@ __global__ __launch_bounds__(2 * kThreads, 1) void attn_bwd_dq_kernel(
 // Merges the parts of every split item (hdr[kFwdSplits] records): dQ is the
 // scaled sum of the parts' fp32 dQ; D_exact = D + the parts' sums of dS gives
 // the -D record of the dK / dV kernel, as the dQ kernel writes it for whole
-// items.  Two threads per row (half of the head dimension each).
+// items.  Split over workgroups and threads as in fwd_combine_kernel.
 template <int D>
 __global__ __launch_bounds__(256) void bwd_dq_combine_kernel(
     const FwdSplit *__restrict__ splits, const int32_t *__restrict__ hdr,
     const float *__restrict__ parts, const float *__restrict__ stats, int h_q, int64_t nq_pad,
     float scale, bf16 *__restrict__ dq, f16 *__restrict__ rec) {
   constexpr size_t PF = fwd_part_floats(D);
-  const int count = hdr[kFwdSplits];
+  constexpr int W = D / kCombineThreads;   // columns of a thread
+  const int count = hdr[kFwdSplits] * kCombineSplit;
   const float s_ov = fp16_scale((uint32_t)hdr[kMaxAbs + 1], true) *
                      fp16_scale((uint32_t)hdr[kMaxAbs + 3], true);
-  const int tid = threadIdx.x, pr = tid >> 1, half = tid & 1;
-  const int w = pr >> 5, r = pr & 31;   // wave slice and row of the item
+  const int tid = threadIdx.x, col = (tid % kCombineThreads) * W;
   for (int e = blockIdx.x; e < count; e += gridDim.x) {
-    const FwdSplit sp = splits[e];
+    const FwdSplit sp = splits[e / kCombineSplit];
+    const int pr = e % kCombineSplit * kCombineRows + tid / kCombineThreads;
+    const int w = pr >> 5, r = pr & 31;   // wave slice and row of the item
     const FwdItem &it = sp.item;
     const int wrow0 = (w / it.nh) * kRows;
     const int wrows = min(max(it.nrows - wrow0, 0), kRows);
     if (r >= wrows) continue;
     const int head = it.head0 + (w % it.nh);
     const int64_t row = (int64_t)it.q_row0 + wrow0 + r;
-    float acc[D / 2];
+    float acc[W];
 #pragma unroll
-    for (int i = 0; i < D / 2; ++i) acc[i] = 0.f;
+    for (int i = 0; i < W; ++i) acc[i] = 0.f;
     float dsum = 0.f;
+#pragma unroll 4
     for (int p = 0; p < sp.parts; ++p) {
       const float *pt = parts + (size_t)(sp.base + p) * PF;
       dsum += pt[(size_t)kFwdPartRows * D + pr];
-      const float4 *src = reinterpret_cast<const float4 *>(pt + (size_t)pr * D + half * (D / 2));
+      const float4 *src = reinterpret_cast<const float4 *>(pt + (size_t)pr * D + col);
 #pragma unroll
-      for (int i = 0; i < D / 8; ++i) {
+      for (int i = 0; i < W / 4; ++i) {
         const float4 x = src[i];
         acc[4 * i] += x.x;
         acc[4 * i + 1] += x.y;
@@ -386,15 +389,15 @@ __global__ __launch_bounds__(256) void bwd_dq_combine_kernel(
         acc[4 * i + 3] += x.w;
       }
     }
-    bf16 *op = dq + ((size_t)row * h_q + head) * D + half * (D / 2);
+    bf16 *op = dq + ((size_t)row * h_q + head) * D + col;
 #pragma unroll
-    for (int i = 0; i < D / 16; ++i) {
-      bf16x8 ov;
+    for (int i = 0; i < W / 4; ++i) {
+      bf16x4 ov;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) ov[j] = static_cast<bf16>(acc[8 * i + j] * scale);
-      *reinterpret_cast<bf16x8 *>(op + 8 * i) = ov;
+      for (int j = 0; j < 4; ++j) ov[j] = static_cast<bf16>(acc[4 * i + j] * scale);
+      *reinterpret_cast<bf16x4 *>(op + 4 * i) = ov;
     }
-    if (half == 0) {
+    if (col == 0) {
       const size_t blk = (size_t)head * (nq_pad / kRows) + row / kRows;
       const float d_exact = stats[blk * 2 * kRows + kRows + row % kRows] + dsum;
       f16x8 dv;
@@ -427,14 +430,14 @@ int launch_bwd_dq(int d, const bf16 *q, const bf16 *dout, const bf16 *k, const b
                        k, v, stats, cu, items, hdr, h_q, h_kv, n_q, n_kv, nq_pad, scale * kLog2e,
                        scale, dq, rec, parts);
     if (max_parts > 0)
-      hipLaunchKernelGGL(bwd_dq_combine_kernel<128>, dim3(blocks), dim3(256), 0, st, splits, hdr,
+      hipLaunchKernelGGL(bwd_dq_combine_kernel<128>, dim3(blocks * 4), dim3(256), 0, st, splits, hdr,
                          parts, stats, h_q, nq_pad, scale, dq, rec);
   } else {
     hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, dim3(blocks), dim3(2 * kThreads), smem, st, q, dout,
                        k, v, stats, cu, items, hdr, h_q, h_kv, n_q, n_kv, nq_pad, scale * kLog2e,
                        scale, dq, rec, parts);
     if (max_parts > 0)
-      hipLaunchKernelGGL(bwd_dq_combine_kernel<64>, dim3(blocks), dim3(256), 0, st, splits, hdr,
+      hipLaunchKernelGGL(bwd_dq_combine_kernel<64>, dim3(blocks * 4), dim3(256), 0, st, splits, hdr,
                          parts, stats, h_q, nq_pad, scale, dq, rec);
   }
   if (tm) hipEventRecord(tm->end, st);

@@ -215,6 +215,11 @@ struct FwdSplit {
 // item's 4 waves x 32 rows (fp32, D per row), then the running max (log2
 // units) and the row sum of P of each of the 128 rows.
 constexpr int kFwdPartRows = 4 * 32;
+// The kernels that merge the parts: workgroups per split item, rows of a
+// workgroup (256 threads), threads of a row.
+constexpr int kCombineSplit = 8;
+constexpr int kCombineRows = kFwdPartRows / kCombineSplit;
+constexpr int kCombineThreads = 256 / kCombineRows;
 constexpr int kFwdSplitMinBlocks = 32;   // a part walks at least 32 key blocks (2048 keys)
 constexpr int kFwdSplitSlots = 3072;     // partial slots of one forward call
 __host__ __device__ constexpr size_t fwd_part_floats(int d) {
