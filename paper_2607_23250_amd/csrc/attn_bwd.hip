@@ -40,6 +40,7 @@
 #include <cstdint>
 
 #include "attn_common.h"
+#include "attn_items.h"
 #include "errors.h"
 
 namespace libra {
@@ -64,20 +65,56 @@ __device__ __forceinline__ unsigned long long group_bits(int hb, int he, int G, 
 // KV heads involved; then items (sample, 128-key block, KV head) ordered by
 // the number of attending rows, longest first, one queue per XCD keyed by
 // (KV head, key block) so that an XCD streams the query blocks of few heads.
-__global__ __launch_bounds__(kPrepThreads) void prep_bwd_kernel(
-    const int64_t *__restrict__ cu, int64_t n, const libra_tile_t *__restrict__ tiles, int64_t T,
-    int h_q, int h_kv, int64_t n_q, int64_t n_kv, int32_t *__restrict__ hdr,
-    int32_t *__restrict__ ext, unsigned long long *__restrict__ gmask,
-    BwdItem *__restrict__ items, int64_t max_items, int grid) {
-  __shared__ int32_t hist[kXcds * kQBuckets];
-  __shared__ int32_t part[kPrepThreads];
+struct BwdPrep {
+  const int64_t *cu;
+  int64_t n;
+  const libra_tile_t *tiles;
+  int64_t T;
+  int h_q, h_kv;
+  int64_t n_q, n_kv;
+  int32_t *hdr;
+  int32_t *ext;
+  unsigned long long *gmask;
+  BwdItem *items;
+  int64_t max_items;
+  int grid;
+};
+constexpr int kExtLds = 1024;   // samples whose extents and head sets are kept in LDS
+constexpr int kMaxLong = 256;
+struct BwdPrepLds {
+  int32_t hist[kXcds * kQBuckets];
+  int32_t part[kPrepThreads];
+  int32_t cu[kCuLds];
+  unsigned long long gmask[kExtLds];
+  int32_t ext[kExtLds];
+  int32_t longs[kMaxLong];
+  int32_t n_long;
+};
+static_assert(sizeof(BwdPrepLds) <= 80 * 1024, "two preparation workgroups fit a CU");
+
+__device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
+  const int64_t n = a.n, T = a.T, n_q = a.n_q, n_kv = a.n_kv;
+  const int h_q = a.h_q, h_kv = a.h_kv;
+  int32_t *hdr = a.hdr;
   const int tid = threadIdx.x;
   const int G = h_q / h_kv;
   const int R = h_kv >= kXcds ? 1 : kXcds / h_kv;
+  const CuView cu = cu_view(a.cu, n, lds.cu);
+  // extents and head sets gather in LDS when they fit, else in the workspace
+  const bool in_lds = n <= kExtLds;
+  int32_t *ext = in_lds ? lds.ext : a.ext;
+  unsigned long long *gmask = in_lds ? lds.gmask : a.gmask;
+  auto fence = [&]() {
+    if (!in_lds) __threadfence();
+    __syncthreads();
+  };
+  auto ext_of = [&](int64_t j) { return in_lds ? lds.ext[j] : ld_agent(&a.ext[j]); };
+  auto gmask_of = [&](int64_t j) { return in_lds ? lds.gmask[j] : ld_agent(&a.gmask[j]); };
   for (int64_t j = tid; j < n; j += kPrepThreads) {
     __hip_atomic_store(&ext[j], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&gmask[j], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  if (tid == 0) lds.n_long = 0;
   if (tid < 6) {
     // the skipped-tile count (counted here for the backward), the odd-heads
     // flag and the max |x| slots
@@ -89,7 +126,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_bwd_kernel(
   int bad = 0;
   bool odd = false;
   for (int64_t t = tid; t < T; t += kPrepThreads) {
-    const libra_tile_t tl = tiles[t];
+    const libra_tile_t tl = a.tiles[t];
     if (!tile_ok(tl, n_q, n_kv, h_q)) {
       ++bad;
       continue;
@@ -103,53 +140,60 @@ __global__ __launch_bounds__(kPrepThreads) void prep_bwd_kernel(
   }
   if (bad) atomicAdd(&hdr[kBadTiles], bad);
   if (odd) atomicOr(&hdr[kOddHeads], 1);
-  __threadfence();
-  __syncthreads();
-  // Samples with more than kCoopBlocks key blocks are enumerated by the
-  // whole workgroup (key blocks across the threads), the others by one
-  // thread each; if the list of long samples overflows, every sample goes the
-  // per-thread way.  Both enumerations below see the same items.
-  constexpr int kCoopBlocks = 64, kMaxLong = 256;
-  __shared__ int32_t longs[kMaxLong];
-  __shared__ int32_t n_long;
-  if (tid == 0) n_long = 0;
-  __syncthreads();
+  fence();
+  // Samples of more than kCoopItems items are enumerated by the whole
+  // workgroup, the others by one wave each; if the list of long samples
+  // overflows, every sample goes to a wave.  Both enumerations below see the
+  // same items.  (One thread per sample took 82 us on a 32K pack, whose 2,100
+  // items lie in 9 samples.)
+  constexpr int kCoopItems = 1024;
+  auto blocks_of = [&](int32_t e) { return (e + kBwdBK - 1) / kBwdBK; };
   for (int64_t j = tid; j < n; j += kPrepThreads) {
-    const int32_t e = ld_agent(&ext[j]);
-    if ((e + kBwdBK - 1) / kBwdBK > kCoopBlocks) {
-      const int32_t slot = atomicAdd(&n_long, 1);
-      if (slot < kMaxLong) longs[slot] = (int32_t)j;
+    const int32_t e = ext_of(j);
+    if (in_lds) a.ext[j] = e;   // for the passes over K and V
+    if ((int64_t)blocks_of(e) * h_kv > kCoopItems) {
+      const int32_t slot = atomicAdd(&lds.n_long, 1);
+      if (slot < kMaxLong) lds.longs[slot] = (int32_t)j;
     }
   }
   __syncthreads();
-  const bool coop = n_long <= kMaxLong;
-  auto emit = [&](auto &&f, int64_t j, int32_t e, int g, int kb) {
-    f(BwdItem{(int32_t)j, kb, g, 0}, (int64_t)(e - kb * kBwdBK + kRows - 1) / kRows,
-      (g * R + kb % R) % kXcds);
+  const bool coop = lds.n_long <= kMaxLong;
+  // item i of sample j: key block i / h_kv of KV head i % h_kv
+  auto emit = [&](auto &&f, int64_t j, int32_t e, unsigned long long mk, int i) {
+    const int kb = i / h_kv, g = i - kb * h_kv;
+    if (mk >> g & 1ull)
+      f(BwdItem{(int32_t)j, kb, g, 0}, (int64_t)(e - kb * kBwdBK + kRows - 1) / kRows,
+        (g * R + kb % R) % kXcds);
   };
   auto each = [&](auto &&f, bool) {
-    for (int64_t j = tid; j < n; j += kPrepThreads) {
-      const int32_t e = ld_agent(&ext[j]);
-      if (e == 0) continue;
-      const int nkb = (e + kBwdBK - 1) / kBwdBK;
-      if (coop && nkb > kCoopBlocks) continue;
-      const unsigned long long mk = ld_agent(&gmask[j]);
-      for (int g = 0; g < h_kv; ++g)
-        if (mk >> g & 1ull)
-          for (int kb = 0; kb < nkb; ++kb) emit(f, j, e, g, kb);
+    for (int64_t j = tid >> 6; j < n; j += kPrepThreads / 64) {
+      const int32_t e = ext_of(j);
+      const int count = blocks_of(e) * h_kv;
+      if (coop && count > kCoopItems) continue;
+      const unsigned long long mk = gmask_of(j);
+      for (int i = tid & 63; i < count; i += 64) emit(f, j, e, mk, i);
     }
     if (!coop) return;
-    for (int i = 0; i < n_long; ++i) {
-      const int64_t j = longs[i];
-      const int32_t e = ld_agent(&ext[j]);
-      const int nkb = (e + kBwdBK - 1) / kBwdBK;
-      const unsigned long long mk = ld_agent(&gmask[j]);
-      for (int g = 0; g < h_kv; ++g)
-        if (mk >> g & 1ull)
-          for (int kb = tid; kb < nkb; kb += kPrepThreads) emit(f, j, e, g, kb);
+    for (int k = 0; k < lds.n_long; ++k) {
+      const int64_t j = lds.longs[k];
+      const int32_t e = ext_of(j);
+      const unsigned long long mk = gmask_of(j);
+      const int count = blocks_of(e) * h_kv;
+      for (int i = tid; i < count; i += kPrepThreads) emit(f, j, e, mk, i);
     }
   };
-  build_queues<BwdItem>(each, hist, part, hdr, kBwdQ, items, max_items, grid);
+  build_queues<BwdItem>(each, lds.hist, lds.part, hdr, kBwdQ, a.items, a.max_items, a.grid);
+}
+
+// Both preparation passes of a call, side by side: workgroup 0 builds the
+// dK / dV items, workgroup 1 the dQ items.
+__global__ __launch_bounds__(kPrepThreads) void prep_bwd_kernel(BwdPrep b, FwdPrep f) {
+  __shared__ union Lds {
+    BwdPrepLds b;
+    FwdPrepLds f;
+  } lds;
+  if (blockIdx.x == 0) prep_bwd(b, lds.b);
+  else prep_fwd(f, lds.f);
 }
 
 // ---------------------------------------------------------------------------
@@ -205,17 +249,18 @@ constexpr int kTileSplit = 64;
 // kernel stages whole records; rows no tile covers must hold finite values,
 // since they meet P = dS = 0 in its products).
 template <int D>
-__global__ __launch_bounds__(256) void bwd_absmax_q_kernel(
-    const bf16 *__restrict__ q, const bf16 *__restrict__ dout,
-    const libra_tile_t *__restrict__ tiles, int h_q, int64_t n_q, int64_t n_kv,
-    int32_t *__restrict__ hdr, f16 *__restrict__ rec) {
+__device__ __forceinline__ void absmax_q(unsigned block, const bf16 *__restrict__ q,
+                                         const bf16 *__restrict__ dout,
+                                         const libra_tile_t *__restrict__ tiles, int h_q,
+                                         int64_t n_q, int64_t n_kv, int32_t *__restrict__ hdr,
+                                         f16 *__restrict__ rec) {
   const int tid = threadIdx.x;
-  const libra_tile_t tl = tiles[blockIdx.x / kTileSplit];
+  const libra_tile_t tl = tiles[block / kTileSplit];
   if (!tile_ok(tl, n_q, n_kv, h_q)) return;
   const int64_t ra = tl.q_row, rb = tl.q_row + (tl.q_end - tl.q_begin);
   const int r = tid >> 3, part = tid & 7;   // 8 threads per row, 32 rows per pass
   float mq = 0.f, mo = 0.f;
-  for (int64_t m = ra / kRows + blockIdx.x % kTileSplit; m * kRows < rb; m += kTileSplit) {
+  for (int64_t m = ra / kRows + block % kTileSplit; m * kRows < rb; m += kTileSplit) {
     const int64_t row = m * kRows + r;
     const bool ok = row >= ra && row < rb;
     for (int h = tl.head_begin; h < tl.head_end; ++h) {
@@ -248,13 +293,15 @@ __global__ __launch_bounds__(256) void bwd_absmax_q_kernel(
 // (all KV heads).  One wave per key row.  CONVERT = false: max |K| and
 // max |V| over them; CONVERT = true: their scaled fp16 copies.
 template <int D, bool CONVERT>
-__global__ __launch_bounds__(256) void bwd_kv_pass_kernel(
-    const bf16 *__restrict__ k, const bf16 *__restrict__ v, const int64_t *__restrict__ cu,
-    int64_t n, const int32_t *__restrict__ ext, int h_kv, int64_t n_kv,
-    int32_t *__restrict__ hdr, f16 *__restrict__ k16, f16 *__restrict__ v16) {
+__device__ __forceinline__ void kv_pass(unsigned block, unsigned blocks,
+                                        const bf16 *__restrict__ k, const bf16 *__restrict__ v,
+                                        const int64_t *__restrict__ cu, int64_t n,
+                                        const int32_t *__restrict__ ext, int h_kv, int64_t n_kv,
+                                        int32_t *__restrict__ hdr, f16 *__restrict__ k16,
+                                        f16 *__restrict__ v16) {
   const int l = threadIdx.x & 63;
-  const int64_t wave = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-  const int64_t waves = (int64_t)gridDim.x * 4;
+  const int64_t wave = ((int64_t)block * 256 + threadIdx.x) >> 6;
+  const int64_t waves = (int64_t)blocks * 4;
   const int chunks = h_kv * D / 8;   // 16-byte chunks of a row
   float mk = 0.f, mv = 0.f, s_k = 1.f, s_v = 1.f;
   if constexpr (CONVERT) {
@@ -308,13 +355,16 @@ __global__ __launch_bounds__(256) void bwd_kv_pass_kernel(
 //     of each block and head for the dQ kernel ("stats",
 //     [h_q][nq_pad / 32][64] floats, so one 256-byte load fetches both).
 template <int D>
-__global__ __launch_bounds__(256) void bwd_pre_kernel(
-    const bf16 *__restrict__ q, const bf16 *__restrict__ o, const bf16 *__restrict__ dout,
-    const float *__restrict__ lse, const libra_tile_t *__restrict__ tiles, int h_q,
-    int64_t n_q, int64_t n_kv, int64_t nq_pad, float scale, const int32_t *__restrict__ hdr,
-    f16 *__restrict__ rec, float *__restrict__ stats) {
+__device__ __forceinline__ void pre_pass(unsigned block, const bf16 *__restrict__ q,
+                                         const bf16 *__restrict__ o,
+                                         const bf16 *__restrict__ dout,
+                                         const float *__restrict__ lse,
+                                         const libra_tile_t *__restrict__ tiles, int h_q,
+                                         int64_t n_q, int64_t n_kv, int64_t nq_pad, float scale,
+                                         const int32_t *__restrict__ hdr,
+                                         f16 *__restrict__ rec, float *__restrict__ stats) {
   const int tid = threadIdx.x;
-  const libra_tile_t tl = tiles[blockIdx.x / kTileSplit];
+  const libra_tile_t tl = tiles[block / kTileSplit];
   if (!tile_ok(tl, n_q, n_kv, h_q)) return;
   const float s_q = fp16_scale((uint32_t)hdr[kMaxAbs + 0], false);
   const float s_o = fp16_scale((uint32_t)hdr[kMaxAbs + 1], true);
@@ -322,7 +372,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(
   const int64_t ra = tl.q_row, rb = tl.q_row + (tl.q_end - tl.q_begin);
   // 8 threads per row, 32 rows per pass
   const int r = tid >> 3, part = tid & 7;
-  for (int64_t m = ra / kRows + blockIdx.x % kTileSplit; m * kRows < rb; m += kTileSplit) {
+  for (int64_t m = ra / kRows + block % kTileSplit; m * kRows < rb; m += kTileSplit) {
     const int64_t row = m * kRows + r;
     const bool ok = row >= ra && row < rb;
     for (int h = tl.head_begin; h < tl.head_end; ++h) {
@@ -366,10 +416,60 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(
   }
 }
 
-__global__ __launch_bounds__(256) void zero_kernel(uint4 *__restrict__ p, int64_t n16) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n16;
-       i += (int64_t)gridDim.x * 256)
+__device__ __forceinline__ void zero_fill(unsigned block, unsigned blocks, uint4 *__restrict__ p,
+                                          int64_t n16) {
+  for (int64_t i = (int64_t)block * 256 + threadIdx.x; i < n16; i += (int64_t)blocks * 256)
     p[i] = make_uint4(0, 0, 0, 0);
+}
+__global__ __launch_bounds__(256) void zero_kernel(uint4 *__restrict__ p, int64_t n16) {
+  zero_fill(blockIdx.x, gridDim.x, p, n16);
+}
+
+// The passes before the dQ and dK / dV kernels, in two launches: what needs
+// nothing but the extents (max |x| of Q, dO, K and V; zero dK and dV in bf16
+// mode), then what needs the maxima (the fp16 copies and records).  Each part
+// takes its own range of workgroups.  In launches of their own, the parts of a
+// 4K pack's backward took 4 to 24 us each for work of 1 to 3 us.
+struct BwdPass {
+  const bf16 *q, *k, *v, *o, *dout;
+  const float *lse;
+  const int64_t *cu;
+  int64_t n;
+  const libra_tile_t *tiles;
+  int h_q, h_kv;
+  int64_t n_q, n_kv, nq_pad;
+  float scale;
+  int32_t *hdr;
+  const int32_t *ext;
+  f16 *rec, *k16, *v16;
+  float *stats;
+  uint4 *dk, *dv;                          // to be zeroed
+  int64_t n16;                             // 16-byte pieces of each
+  unsigned tile_blocks, kv_blocks, zero_blocks;
+};
+template <int D>
+__global__ __launch_bounds__(256) void bwd_max_kernel(BwdPass a) {
+  unsigned b = blockIdx.x;
+  if (b < a.kv_blocks) {
+    kv_pass<D, false>(b, a.kv_blocks, a.k, a.v, a.cu, a.n, a.ext, a.h_kv, a.n_kv, a.hdr, a.k16,
+                      a.v16);
+  } else if ((b -= a.kv_blocks) < a.tile_blocks) {
+    absmax_q<D>(b, a.q, a.dout, a.tiles, a.h_q, a.n_q, a.n_kv, a.hdr, a.rec);
+  } else {
+    b -= a.tile_blocks;
+    const unsigned half = a.zero_blocks / 2;
+    zero_fill(b % half, half, b < half ? a.dk : a.dv, a.n16);
+  }
+}
+template <int D>
+__global__ __launch_bounds__(256) void bwd_copy_kernel(BwdPass a) {
+  const unsigned b = blockIdx.x;
+  if (b < a.kv_blocks)
+    kv_pass<D, true>(b, a.kv_blocks, a.k, a.v, a.cu, a.n, a.ext, a.h_kv, a.n_kv, a.hdr, a.k16,
+                     a.v16);
+  else
+    pre_pass<D>(b - a.kv_blocks, a.q, a.o, a.dout, a.lse, a.tiles, a.h_q, a.n_q, a.n_kv, a.nq_pad,
+                a.scale, a.hdr, a.rec, a.stats);
 }
 
 // ---------------------------------------------------------------------------
@@ -919,35 +1019,49 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
       return fail(LIBRA_EHIP, "hipFuncSetAttribute failed");
     attr_set = true;
   }
-  if (!accumulate) {
-    const int64_t n16 = n_kv * h_kv * D * (int64_t)sizeof(bf16) / 16;
-    const unsigned blocks = (unsigned)std::min<int64_t>((n16 + 255) / 256, 4096);
-    hipLaunchKernelGGL(zero_kernel, dim3(blocks), dim3(256), 0, st, static_cast<uint4 *>(dk), n16);
-    hipLaunchKernelGGL(zero_kernel, dim3(blocks), dim3(256), 0, st, static_cast<uint4 *>(dv), n16);
+  // bf16 dK / dV are written where a covered row attends and zero elsewhere
+  const int64_t n16 = accumulate ? 0 : n_kv * h_kv * D * (int64_t)sizeof(bf16) / 16;
+  const unsigned zero_blocks = (unsigned)std::min<int64_t>((n16 + 255) / 256, 4096);
+  if (T == 0 && n16 > 0) {
+    hipLaunchKernelGGL(zero_kernel, dim3(zero_blocks), dim3(256), 0, st, static_cast<uint4 *>(dk),
+                       n16);
+    hipLaunchKernelGGL(zero_kernel, dim3(zero_blocks), dim3(256), 0, st, static_cast<uint4 *>(dv),
+                       n16);
   }
   if (T > 0) {
     int dev = 0, cus = 256;
     hipGetDevice(&dev);
     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    hipLaunchKernelGGL(prep_bwd_kernel, dim3(1), dim3(kPrepThreads), 0, st, cu, n, tiles, T, h_q,
-                       h_kv, n_q, n_kv, hdr, ext, gmask, items, L.max_items, cus);
     // the dQ kernel runs one workgroup per CU; its items split K like the
-    // forward's when there are few of them
+    // forward's when there are few of them, but only when whole rounds of items
+    // would leave workgroups idle: measured on calls of one tile, splitting
+    // items that already fill the grid cost dQ 2-4%, while the forward gained
+    // 3-5% from it
     auto *splits = reinterpret_cast<FwdSplit *>(ws + L.splits);
     float *parts = reinterpret_cast<float *>(ws + L.parts);
-    enqueue_fwd_items(cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, qitems, L.max_qitems, false,
-                      cus, L.max_parts, splits, st);
-    hipLaunchKernelGGL(bwd_absmax_q_kernel<D>, dim3((unsigned)(T * kTileSplit)), dim3(256), 0, st,
-                       q, dout, tiles, h_q, n_q, n_kv, hdr, rec);
-    hipLaunchKernelGGL((bwd_kv_pass_kernel<D, false>), dim3((unsigned)cus * 8), dim3(256), 0, st,
-                       k, v, cu, n, ext, h_kv, n_kv, hdr, k16, v16);
-    hipLaunchKernelGGL((bwd_kv_pass_kernel<D, true>), dim3((unsigned)cus * 8), dim3(256), 0, st,
-                       k, v, cu, n, ext, h_kv, n_kv, hdr, k16, v16);
-    hipLaunchKernelGGL(bwd_pre_kernel<D>, dim3((unsigned)(T * kTileSplit)), dim3(256), 0, st, q,
-                       o, dout, lse, tiles, h_q, n_q, n_kv, L.nq_pad, scale, hdr, rec, stats);
+    const int max_parts = may_split(n_kv) ? L.max_parts : 0;
+    hipLaunchKernelGGL(prep_bwd_kernel, dim3(2), dim3(kPrepThreads), 0, st,
+                       BwdPrep{cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, ext, gmask, items,
+                               L.max_items, cus},
+                       FwdPrep{cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, qitems, L.max_qitems, 0,
+                               cus, max_parts, 1, splits});
+    // K and V rows: at least eight for a wave (every workgroup that finds a new
+    // maximum posts an atomic on the same two slots: 2048 of them took 24 us on
+    // 4096 rows)
+    const unsigned kv_blocks =
+        (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_kv + 31) / 32, (int64_t)cus * 8));
+    const BwdPass pass{q, k, v, o, dout, lse, cu, n, tiles, h_q, h_kv, n_q, n_kv, L.nq_pad, scale,
+                       hdr, ext, rec, k16, v16, stats, static_cast<uint4 *>(dk),
+                       static_cast<uint4 *>(dv), n16, (unsigned)(T * kTileSplit), kv_blocks,
+                       2 * zero_blocks};
+    hipLaunchKernelGGL(bwd_max_kernel<D>,
+                       dim3(pass.kv_blocks + pass.tile_blocks + pass.zero_blocks), dim3(256), 0,
+                       st, pass);
+    hipLaunchKernelGGL(bwd_copy_kernel<D>, dim3(pass.kv_blocks + pass.tile_blocks), dim3(256), 0,
+                       st, pass);
     // dQ first: it writes the -D records the dK / dV kernel reads
     const int rc = launch_bwd_dq(D, q, dout, k, v, stats, cu, qitems, hdr, h_q, h_kv, n_q, n_kv,
-                                 L.nq_pad, scale, dq, rec, splits, parts, L.max_parts, cus,
+                                 L.nq_pad, scale, dq, rec, splits, parts, max_parts, cus,
                                  st, tm_q);
     if (rc != LIBRA_OK) return rc;
     if (tm_kv) hipEventRecord(tm_kv->begin, st);

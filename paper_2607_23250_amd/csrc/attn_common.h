@@ -94,15 +94,20 @@ __device__ void build_queues(Each &&each, int32_t *hist, int32_t *part, int32_t 
   constexpr int per = kXcds * kQBuckets / kPrepThreads;
   int32_t s = 0;
   for (int i = 0; i < per; ++i) s += hist[tid * per + i];
-  part[tid] = s;
-  __syncthreads();
-  for (int o = 1; o < kPrepThreads; o <<= 1) {
-    const int32_t v = tid >= o ? part[tid - o] : 0;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
+  // inclusive scan over the workgroup: inside each wave, then over the waves
+  int32_t inc = s;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t v = __shfl_up(inc, o);
+    if ((tid & 63) >= o) inc += v;
   }
-  int32_t pos = part[tid] - s;
+  if ((tid & 63) == 63) part[tid >> 6] = inc;
+  __syncthreads();
+  int32_t before = 0;
+  for (int i = 0; i < (tid >> 6); ++i) before += part[i];
+  __syncthreads();
+  part[tid] = inc += before;
+  __syncthreads();
+  int32_t pos = inc - s;
   constexpr int threads_per_queue = kPrepThreads / kXcds;
   if (tid % threads_per_queue == 0) {
     const int x = tid / threads_per_queue;
@@ -222,6 +227,11 @@ constexpr int kCombineRows = kFwdPartRows / kCombineSplit;
 constexpr int kCombineThreads = 256 / kCombineRows;
 constexpr int kFwdSplitMinBlocks = 32;   // a part walks at least 32 key blocks (2048 keys)
 constexpr int kFwdSplitSlots = 3072;     // partial slots of one forward call
+// Can a call split an item?  Only one whose first row lies at least two parts
+// into its sample, so the samples' rows have to reach past that.
+__host__ __device__ constexpr bool may_split(int64_t n_kv) {
+  return n_kv > 2 * (int64_t)kFwdSplitMinBlocks * kFwdBN;
+}
 __host__ __device__ constexpr size_t fwd_part_floats(int d) {
   return (size_t)kFwdPartRows * (size_t)(d + 2);
 }
@@ -612,8 +622,26 @@ __device__ __forceinline__ f32x16 mfma_zero_c() {
   return c;
 }
 
+// cu_seqlens as the preparation pass reads it: from LDS (positions fit 32
+// bits) when there are at most kCuLds entries, else from memory.  Its binary
+// searches are chains of dependent reads, each about 0.5 us from memory.
+constexpr int kCuLds = 2048;
+struct CuView {
+  const int64_t *g;
+  const int32_t *s;   // LDS copy, or nullptr
+  __device__ __forceinline__ int64_t operator[](int64_t j) const { return s ? s[j] : g[j]; }
+};
+// Copies cu[0 .. n] if it fits (followed by a barrier of the caller's).
+__device__ __forceinline__ CuView cu_view(const int64_t *cu, int64_t n, int32_t *lds) {
+  const bool fits = n < kCuLds;
+  if (fits)
+    for (int i = threadIdx.x; i <= (int)n; i += kPrepThreads) lds[i] = (int32_t)cu[i];
+  return CuView{cu, fits ? lds : nullptr};
+}
+
 // First index i in [0, n] with a[i] > x (a sorted ascending, n+1 entries read at most n).
-__device__ __forceinline__ int64_t upper_bound64(const int64_t *a, int64_t n, int64_t x) {
+template <typename A>
+__device__ __forceinline__ int64_t upper_bound64(const A &a, int64_t n, int64_t x) {
   int64_t lo = 0, hi = n;
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
@@ -655,17 +683,6 @@ struct KernelTimer {
   hipEvent_t begin = nullptr, end = nullptr;
 };
 
-// Shared preparation pass (attn_fwd.hip): forward-style work items, also
-// used by the dQ kernel.
-// Forward-style items for the dQ kernel's `grid` workgroups, split K as in
-// the forward when max_parts > 0 (split records into `splits`), but only when
-// whole rounds of items would leave workgroups idle: measured on calls of one
-// tile, splitting items that already fill the grid cost dQ 2-4%, while the
-// forward gained 3-5% from it.
-void enqueue_fwd_items(const int64_t *cu, int64_t n, const libra_tile_t *tiles, int64_t T,
-                       int h_q, int h_kv, int64_t n_q, int64_t n_kv, int32_t *hdr,
-                       FwdItem *items, int64_t max_items, bool count_bad, int grid,
-                       int max_parts, FwdSplit *splits, hipStream_t st);
 int64_t fwd_max_items(int64_t T, int64_t n, int64_t n_q, int h_q, int h_kv);
 
 int launch_fwd(const void *q, const void *k, const void *v, const int64_t *cu, int64_t n,
