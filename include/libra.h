@@ -268,6 +268,12 @@ int libra_attn_fwd_noalloc(const void *q, const void *k, const void *v,
  * forward does, when the call's items would leave more than a tenth of the
  * workgroups idle; the parts' fp32 dQ and sums of dS are merged before the
  * dK / dV products read D.  The workspace holds those partial results too.
+ * Split rows: the dK / dV products cut their work items (128 keys of a KV head
+ * against all rows that attend them) into row ranges when the longest item
+ * would take a quarter longer than an even spread of the call's work (few
+ * samples and KV heads).  Their fp32 partial sums are added in row order, so
+ * the result is the same up to the order of fp32 additions, and the same from
+ * one call to the next.
  */
 int libra_attn_bwd(const void *q, const void *k, const void *v, const void *o, const float *lse,
                    const void *dout, const int64_t *cu_seqlens, int64_t num_samples,

@@ -78,6 +78,7 @@ struct BwdPrep {
   BwdItem *items;
   int64_t max_items;
   int grid;
+  BwdSplit *splits;
 };
 constexpr int kExtLds = 1024;   // samples whose extents and head sets are kept in LDS
 constexpr int kMaxLong = 256;
@@ -88,7 +89,8 @@ struct BwdPrepLds {
   unsigned long long gmask[kExtLds];
   int32_t ext[kExtLds];
   int32_t longs[kMaxLong];
-  int32_t n_long;
+  int32_t n_long, longest, chunk, nslot, nsplit;
+  unsigned long long work, parts;
 };
 static_assert(sizeof(BwdPrepLds) <= 80 * 1024, "two preparation workgroups fit a CU");
 
@@ -114,7 +116,10 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
     __hip_atomic_store(&ext[j], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&gmask[j], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (tid == 0) lds.n_long = 0;
+  if (tid == 0) {
+    lds.n_long = lds.longest = lds.chunk = lds.nslot = lds.nsplit = 0;
+    lds.work = 0;
+  }
   if (tid < 6) {
     // the skipped-tile count (counted here for the backward), the odd-heads
     // flag and the max |x| slots
@@ -162,10 +167,11 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
   auto emit = [&](auto &&f, int64_t j, int32_t e, unsigned long long mk, int i) {
     const int kb = i / h_kv, g = i - kb * h_kv;
     if (mk >> g & 1ull)
-      f(BwdItem{(int32_t)j, kb, g, 0}, (int64_t)(e - kb * kBwdBK + kRows - 1) / kRows,
+      f(BwdItem{(int32_t)j, kb, g, -1, 0, INT32_MAX, 0, 0}, (e - kb * kBwdBK + kRows - 1) / kRows,
         (g * R + kb % R) % kXcds);
   };
-  auto each = [&](auto &&f, bool) {
+  // every whole item once: f(item, row blocks, queue)
+  auto whole = [&](auto &&f) {
     for (int64_t j = tid >> 6; j < n; j += kPrepThreads / 64) {
       const int32_t e = ext_of(j);
       const int count = blocks_of(e) * h_kv;
@@ -182,7 +188,71 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
       for (int i = tid; i < count; i += kPrepThreads) emit(f, j, e, mk, i);
     }
   };
+  // Split rows: when the longest item takes a quarter longer than the whole
+  // call would if its work were spread evenly (few KV heads and samples: a 4K
+  // pack has 70 items for 256 workgroups), the items longer than half of a
+  // workgroup's share are cut into parts of C row blocks, summed by
+  // bwd_dkdv_combine_kernel.  C is at least kBwdSplitMinBlocks and doubles
+  // until the parts fit the slots.  Below that line a part's own cost (K / V
+  // loads, the fill of the ring, fp32 sums written and read) takes the gain:
+  // 46 row blocks against a share of 4.6 (4K tokens, 2 KV heads, d = 64): 119 us
+  // whole, 51 split; 430 against 391 (20K tokens, 4 KV heads): 908 and 935.
+  {
+    unsigned long long w = 0;
+    int32_t m = 0;
+    whole([&](const BwdItem &, int cost, int) {
+      w += (unsigned long long)cost;
+      m = max(m, cost);
+    });
+    if (m) {
+      atomicAdd(&lds.work, w);
+      atomicMax(&lds.longest, m);
+    }
+  }
+  __syncthreads();
+  const unsigned long long half = lds.work / (2ull * (unsigned)a.grid);
+  if (4ull * (unsigned)lds.longest * (unsigned)a.grid > 5ull * lds.work &&
+      lds.longest >= 2 * kBwdSplitMinBlocks) {
+    int c = (int)max(half, (unsigned long long)kBwdSplitMinBlocks);
+    for (;; c *= 2) {   // ends: no item is longer than 2^26 blocks
+      if (tid == 0) lds.parts = 0;
+      __syncthreads();
+      whole([&](const BwdItem &, int cost, int) {
+        if (cost > c) atomicAdd(&lds.parts, (unsigned long long)((cost + c - 1) / c));
+      });
+      __syncthreads();
+      const bool fits = lds.parts <= (unsigned long long)kBwdSplitSlots;
+      __syncthreads();
+      if (fits) break;
+    }
+    if (tid == 0) lds.chunk = c;
+  }
+  __syncthreads();
+  const int chunk = lds.chunk;   // 0: no item is split
+  auto each = [&](auto &&f, bool scatter) {
+    whole([&](const BwdItem &it, int cost, int x) {
+      if (chunk == 0 || cost <= chunk) {
+        f(it, (int64_t)cost, x);
+        return;
+      }
+      const int np = (cost + chunk - 1) / chunk, per = (cost + np - 1) / np;
+      int32_t base = 0;
+      if (scatter) {
+        base = atomicAdd(&lds.nslot, np);
+        a.splits[atomicAdd(&lds.nsplit, 1)] = BwdSplit{it, base, np, 0, 0};
+      }
+      for (int p = 0; p < np; ++p) {
+        BwdItem ip = it;
+        ip.slot = base + p;
+        ip.r0 = it.kb * kBwdBK + kRows * per * p;
+        if (p + 1 < np) ip.r1 = ip.r0 + kRows * per;
+        f(ip, (int64_t)(p + 1 < np ? per : max(cost - per * p, 1)), x);
+      }
+    });
+  };
   build_queues<BwdItem>(each, lds.hist, lds.part, hdr, kBwdQ, a.items, a.max_items, a.grid);
+  __syncthreads();
+  if (tid == 0) hdr[kBwdSplits] = lds.nsplit;
 }
 
 // Both preparation passes of a call, side by side: workgroup 0 builds the
@@ -494,7 +564,7 @@ struct KvShape {
 // running 64-bit record offset.
 struct StepIter {
   const libra_tile_t *tiles;
-  int64_t T, n_q, n_kv, key0, len;
+  int64_t T, n_q, n_kv, key0, p0, p1;   // rows at positions [p0, p1)
   int h_q, g, G, kloc0, rbytes;   // rbytes: of a record
   // fragment
   int64_t t;                // tile index
@@ -509,8 +579,8 @@ struct StepIter {
     for (; t < T; ++t) {
       const libra_tile_t tl = tiles[t];
       if (!tile_ok(tl, n_q, n_kv, h_q)) continue;
-      const int64_t pb = tl.q_begin > key0 ? tl.q_begin : key0;
-      const int64_t pe = tl.q_end < key0 + len ? tl.q_end : key0 + len;
+      const int64_t pb = tl.q_begin > p0 ? tl.q_begin : p0;
+      const int64_t pe = tl.q_end < p1 ? tl.q_end : p1;
       if (pb >= pe) continue;
       h0 = max(tl.head_begin, g * G);
       h1 = min(tl.head_end, (g + 1) * G);
@@ -559,7 +629,7 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
     const int64_t *__restrict__ cu, const libra_tile_t *__restrict__ tiles, int64_t T,
     const BwdItem *__restrict__ items, int32_t *__restrict__ hdr, int h_q, int h_kv,
     int64_t n_q, int64_t n_kv, float scale, float c2, void *__restrict__ dk_out,
-    void *__restrict__ dv_out, int accumulate) {
+    void *__restrict__ dv_out, int accumulate, float *__restrict__ parts) {
   using S = KvShape<D>;
   extern __shared__ __attribute__((aligned(16))) bf16 smem[];
   __shared__ int32_t s_item;
@@ -863,8 +933,8 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
     // Steps are walked once, at issue; what the compute side needs of the step
     // in ring stage j (lo | hi << 8 | two << 16, and the q_loc of the block's
     // row 0) waits in lane j of desc / desc_qb.
-    StepIter iss{tiles, T, n_q, n_kv, key0, len, h_q, g, G, kloc0,
-                 2 * S::HEAD_EL};
+    StepIter iss{tiles, T, n_q, n_kv, key0, key0 + item.r0,
+                 key0 + (item.r1 < len ? item.r1 : len), h_q, g, G, kloc0, 2 * S::HEAD_EL};
     iss.start();
     int desc = 0, desc_qb = 0;
     int issued = 0, computed = 0;
@@ -935,7 +1005,20 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
     }
 
     // ---- write dK, dV for this wave's 32 keys
-    if (key_ok) {
+    if (key_ok && item.slot >= 0) {
+      // a part of a split item: unscaled fp32 dK and dV (key 32 w + ln)
+      float *op = parts + (size_t)item.slot * 2 * fwd_part_floats(D) + (size_t)(32 * w + ln) * D +
+                  8 * kg;
+      static_for<D / 32>([&](auto dt) {
+        static_for<4>([&](auto q4) {
+          constexpr int at = 32 * dt + 16 * (q4 >> 1) + 4 * (q4 & 1), r0 = 4 * q4;
+          *reinterpret_cast<float4 *>(op + at) = make_float4(
+              dka[dt][r0], dka[dt][r0 + 1], dka[dt][r0 + 2], dka[dt][r0 + 3]);
+          *reinterpret_cast<float4 *>(op + fwd_part_floats(D) + at) = make_float4(
+              dva[dt][r0], dva[dt][r0 + 1], dva[dt][r0 + 2], dva[dt][r0 + 3]);
+        });
+      });
+    } else if (key_ok) {
       const size_t base = ((size_t)krow * h_kv + g) * D + 8 * kg;
       static_for<D / 32>([&](auto dt) {
         static_for<2>([&](auto hh) {
@@ -970,12 +1053,76 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
   }
 }
 
+// Sums the parts of every split dK / dV item (hdr[kBwdSplits] records) in row
+// order and writes dK and dV as the kernel does for whole items.  Work shared
+// as in fwd_combine_kernel (16 keys to a workgroup, 16 threads to a key).
+template <int D>
+__global__ __launch_bounds__(256) void bwd_dkdv_combine_kernel(
+    const BwdSplit *__restrict__ splits, const int32_t *__restrict__ hdr,
+    const float *__restrict__ parts, const int64_t *__restrict__ cu, int h_kv, float scale,
+    void *__restrict__ dk_out, void *__restrict__ dv_out, int accumulate) {
+  constexpr size_t PF = fwd_part_floats(D);
+  constexpr int W = D / kCombineThreads;   // columns of a thread
+  const int count = hdr[kBwdSplits] * kCombineSplit;
+  const float s_q = fp16_scale((uint32_t)hdr[kMaxAbs + 0], false);
+  const float s_o = fp16_scale((uint32_t)hdr[kMaxAbs + 1], true);
+  const float s_v = fp16_scale((uint32_t)hdr[kMaxAbs + 3], true);
+  const float mul[2] = {scale / (s_q * s_o * s_v), 1.f / s_o};   // as in the kernel
+  const int tid = threadIdx.x, col = (tid % kCombineThreads) * W;
+  for (int e = blockIdx.x; e < count; e += gridDim.x) {
+    const BwdSplit sp = splits[e / kCombineSplit];
+    const int kr = e % kCombineSplit * kCombineRows + tid / kCombineThreads;
+    const int64_t key0 = cu[sp.item.sample], key = key0 + (int64_t)sp.item.kb * kBwdBK + kr;
+    if (key >= cu[sp.item.sample + 1]) continue;
+    const float *src = parts + (size_t)sp.base * 2 * PF + (size_t)kr * D + col;
+    float acc[2][W];
+#pragma unroll
+    for (int i = 0; i < 2 * W; ++i) acc[i / W][i % W] = 0.f;
+#pragma unroll 4
+    for (int p = 0; p < sp.parts; ++p) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int i = 0; i < W / 4; ++i) {
+          const float4 v = *reinterpret_cast<const float4 *>(src + (2 * p + x) * PF + 4 * i);
+          acc[x][4 * i] += v.x;
+          acc[x][4 * i + 1] += v.y;
+          acc[x][4 * i + 2] += v.z;
+          acc[x][4 * i + 3] += v.w;
+        }
+    }
+    const size_t off = ((size_t)key * h_kv + sp.item.g) * D + col;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      void *out = x ? dv_out : dk_out;
+#pragma unroll
+      for (int i = 0; i < W / 4; ++i) {
+        if (accumulate) {
+          float4 *op = reinterpret_cast<float4 *>(static_cast<float *>(out) + off) + i;
+          float4 a = *op;
+          a.x += acc[x][4 * i] * mul[x];
+          a.y += acc[x][4 * i + 1] * mul[x];
+          a.z += acc[x][4 * i + 2] * mul[x];
+          a.w += acc[x][4 * i + 3] * mul[x];
+          *op = a;
+        } else {
+          bf16x4 v;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = static_cast<bf16>(acc[x][4 * i + j] * mul[x]);
+          *reinterpret_cast<bf16x4 *>(static_cast<bf16 *>(out) + off + 4 * i) = v;
+        }
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 static size_t align256b(size_t x) { return (x + 255) / 256 * 256; }
 
 BwdLayout bwd_layout(int64_t T, int64_t n, int64_t n_q, int64_t n_kv, int h_q, int h_kv, int d) {
   BwdLayout L;
-  L.max_items = (n_kv / kBwdBK + n + 1) * (int64_t)h_kv;
+  // a split item's parts take its place: kBwdSplitSlots of them at most
+  L.max_items = (n_kv / kBwdBK + n + 1) * (int64_t)h_kv + kBwdSplitSlots;
   L.max_qitems = fwd_max_items(T, n, n_q, h_q, h_kv);
   L.nq_pad = (n_q + kRows - 1) / kRows * kRows;
   L.hdr = 0;
@@ -990,7 +1137,9 @@ BwdLayout bwd_layout(int64_t T, int64_t n, int64_t n_q, int64_t n_kv, int h_q, i
   L.stats = align256b(L.v16 + (size_t)n_kv * h_kv * d * sizeof(f16));
   L.splits = align256b(L.stats + (size_t)h_q * L.nq_pad * 2 * sizeof(float));
   L.max_parts = kFwdSplitSlots;
-  L.parts = align256b(L.splits + (size_t)(L.max_parts / 2) * sizeof(FwdSplit));
+  L.bsplits = align256b(L.splits + (size_t)(L.max_parts / 2) * sizeof(FwdSplit));
+  // the partial slots serve the dQ kernel, then the dK / dV kernel
+  L.parts = align256b(L.bsplits + (size_t)(kBwdSplitSlots / 2) * sizeof(BwdSplit));
   L.total = align256b(L.parts + (size_t)L.max_parts * fwd_part_floats(d) * sizeof(float));
   return L;
 }
@@ -1042,7 +1191,7 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
     const int max_parts = may_split(n_kv) ? L.max_parts : 0;
     hipLaunchKernelGGL(prep_bwd_kernel, dim3(2), dim3(kPrepThreads), 0, st,
                        BwdPrep{cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, ext, gmask, items,
-                               L.max_items, cus},
+                               L.max_items, cus, reinterpret_cast<BwdSplit *>(ws + L.bsplits)},
                        FwdPrep{cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, qitems, L.max_qitems, 0,
                                cus, max_parts, 1, splits});
     // K and V rows: at least eight for a wave (every workgroup that finds a new
@@ -1067,7 +1216,10 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
     if (tm_kv) hipEventRecord(tm_kv->begin, st);
     hipLaunchKernelGGL(attn_bwd_dkdv_kernel<D>, dim3(cus), dim3(kThreads), KvShape<D>::SMEM, st,
                        k16, v16, rec, cu, tiles, T, items, hdr, h_q, h_kv, n_q, n_kv, scale,
-                       scale * kLog2e, dk, dv, accumulate ? 1 : 0);
+                       scale * kLog2e, dk, dv, accumulate ? 1 : 0, parts);
+    hipLaunchKernelGGL(bwd_dkdv_combine_kernel<D>, dim3(cus * 4), dim3(256), 0, st,
+                       reinterpret_cast<const BwdSplit *>(ws + L.bsplits), hdr, parts, cu, h_kv,
+                       scale, dk, dv, accumulate ? 1 : 0);
     if (tm_kv) hipEventRecord(tm_kv->end, st);
   }
   const hipError_t e = hipGetLastError();

@@ -45,6 +45,7 @@ constexpr int kPrepThreads = 1024;
 enum HdrSlot {
   kBadTiles = 4,   // tiles skipped because they were out of range (+1 on item overflow)
   kOddHeads = 5,   // backward: some tile covers an odd number of a KV group's heads
+  kBwdSplits = 6,  // backward: split dK / dV items (BwdSplit records)
   kFwdQ = 8,       // forward / dQ work items
   kBwdQ = 32,      // dK/dV work items
   kMaxAbs = 56,    // backward: max |x| (fp32 bits) of Q, dO, K, V in slots 56..59
@@ -237,13 +238,28 @@ __host__ __device__ constexpr size_t fwd_part_floats(int d) {
 }
 
 // One backward work item: 128 keys (block kb, anchored at the sample start)
-// of KV head g of sample j.
+// of KV head g of sample j, against the sample's rows [r0, r1) (a whole item:
+// all of them).  A part of a split item leaves its fp32 dK and dV in partial
+// slots 2 slot and 2 slot + 1 (-1: a whole item, which writes dK and dV itself).
 struct BwdItem {
   int32_t sample;
   int32_t kb;
   int32_t g;
-  int32_t pad;
+  int32_t slot;
+  int32_t r0;
+  int32_t r1;
+  int32_t pad0, pad1;
 };
+static_assert(sizeof(BwdItem) == 32, "item layout");
+// A split dK / dV item and its partial slots [base, base + parts), in row order.
+struct BwdSplit {
+  BwdItem item;
+  int32_t base;
+  int32_t parts;
+  int32_t pad0, pad1;
+};
+constexpr int kBwdSplitMinBlocks = 8;              // a part walks at least 8 row blocks
+constexpr int kBwdSplitSlots = kFwdSplitSlots / 2; // a part takes two slots
 
 // Swap bits 2 and 3 of a row index: reading MFMA operand rows in this order
 // makes the 16 accumulator registers of a lane hold 8 + 8 contiguous rows.
@@ -667,7 +683,7 @@ struct FwdLayout {
 };
 struct BwdLayout {
   size_t hdr = 0, ext = 0, gmask = 0, items = 0, qitems = 0, rec = 0, k16 = 0,
-         v16 = 0, stats = 0, splits = 0, parts = 0, total = 0;
+         v16 = 0, stats = 0, splits = 0, bsplits = 0, parts = 0, total = 0;
   int32_t max_parts = 0;   // split-K partial slots of the dQ kernel
   int64_t max_items = 0, max_qitems = 0, nq_pad = 0;
 };

@@ -79,3 +79,28 @@ def test_head_ranges_and_shared_row_blocks(cuts, d):
         spans += [(x, y, a, b) for x, y in zip(rows[:-1], rows[1:])]
     say(f"[head ranges] {cuts} d={d} rows={n} tiles={len(spans)}")
     _check(lengths, _tiles(spans), 8, 2, d)
+
+
+@pytest.mark.parametrize("h_q,h_kv,d,n", [(2, 1, 64, 511), (4, 2, 128, 513), (3, 1, 64, 1200),
+                                          (2, 2, 128, 2049), (8, 2, 64, 4096)])
+def test_few_long_kv_items_split_rows(h_q, h_kv, d, n):
+    """One or two samples and few KV heads: the dK / dV items are longer than
+    the share of a workgroup and are cut into row ranges whose partial sums are
+    merged; 511 rows are just below two parts.  Tiles that end inside the
+    parts; both output modes; the same bits from one call to the next."""
+    lengths = [n, 77]
+    rows = n + 77
+    spans = [(a, min(a + 301, rows), 0, h_q) for a in range(0, rows, 301)]
+    tiles = _tiles(spans)
+    say(f"[row split] heads=({h_q},{h_kv}) d={d} rows={rows}")
+    _check(lengths, tiles, h_q, h_kv, d)
+    q, k, v, do = (t.to(DEV) for t in wl.tensors(5, rows, rows, h_q, h_kv, d))
+    cu = torch.tensor([0, n, rows], dtype=torch.int64, device=DEV)
+    td = pl.tiles_to_device(tiles, DEV)
+    o, lse = pl.libra_attn_fwd(q, k, v, cu, td)
+    a, b = (pl.libra_attn_bwd(q, k, v, o, lse, do, cu, td) for _ in range(2))
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+    _, dK, dV = oa.attention_bwd(q.cpu(), k.cpu(), v.cpu(), do.cpu(), lengths, np.arange(rows))
+    check("dK", to_np(a[1]), dK, bf16_out=True)
+    check("dV", to_np(a[2]), dV, bf16_out=True)
