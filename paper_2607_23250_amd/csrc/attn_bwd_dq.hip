@@ -42,7 +42,12 @@ struct DqShape {
 // behind, with its dS^T straight from registers (the S^T rows are ordered so
 // that its accumulators are the B operand of the dQ^T products).  The two
 // halves of a slice add up their dQ^T and sums of dS at the end of the item.
-// One barrier per block; a 4-stage K / V ring (block i read by the S^T and
+// The kernel runs at the power limit of the card (6 d flops per pair at 1.25
+// PFLOP/s, against 1.56 of a large matrix product), so what it saves in
+// instructions shows little: operand addresses from two registers instead of
+// eight (swu, which also ended the spills) and reads four products ahead
+// instead of three took 4.03 ms to 4.00 on a 32K pack, 64.8 to 64.6 on the 256K
+// share.  One barrier per block; a 4-stage K / V ring (block i read by the S^T and
 // dP^T products, block i - 1 by the dQ^T products, blocks i + 1 and i + 2
 // land).
 template <int D>
@@ -64,26 +69,23 @@ __global__ __launch_bounds__(2 * kThreads, 1) void attn_bwd_dq_kernel(
   int q_state = kTakeFirst;
   const float s_ov = fp16_scale((uint32_t)hdr[kMaxAbs + 1], true) *
                      fp16_scale((uint32_t)hdr[kMaxAbs + 3], true);
-  // staging: wave load u covers rows (wv + 8u) * 64 / KC + l / KC of a tile
-  auto kst = [&](int u) { return (wv + S::NW * u) * (64 / S::KC) + l / S::KC; };
+  // staging: wave load u fills unit wv + 8 u of a tile
   uint32_t k_lane[S::NK];
   static_for<S::NK>([&](auto u) {
-    const int r = kst(u);
-    k_lane[u] = 2u * (uint32_t)(r * h_kv * D + 8 * swt<S::KC>(r, l % S::KC));
+    const int wl = wv + S::NW * u;
+    k_lane[u] = 2u * (uint32_t)(swu_row<S::KC>(wl, l) * h_kv * D + 8 * swu_col<S::KC>(wl, l));
   });
+  // row reads: chunk 2 c + kg, one offset per parity of c, then 4 chunks per 2
+  // steps of c; transpose reads of the K^T operands (key chunk 2 hf + c of the
+  // block): one offset per half, then 4 chunks per step of dt
+  constexpr int STEP4 = S::KC == 16 ? 128 : 256;   // elements from chunk j to chunk j + 4
   const int prow = perm32(ln) + 32 * hf;
-  int koff[D / 16];
-  static_for<D / 16>([&](auto c) { koff[c] = prow * D + 8 * swt<S::KC>(prow, 2 * c + kg); });
-  // transpose reads of the K^T operands (key chunk 2 hf + c of the block)
-  int troff[D / 32][2];
+  const int koff[2] = {swu<S::KC>(prow, kg), swu<S::KC>(prow, 2 + kg)};
+  int troff[2];
   {
     const int grp = l >> 4, i = (l & 15) >> 2, r = l & 3;
-    static_for<D / 32>([&](auto dt) {
-      static_for<2>([&](auto h2) {
-        const int row = 8 * (grp >> 1) + 4 * h2 + i;
-        const int chunk = 4 * dt + 2 * (grp & 1) + (r & 1);
-        troff[dt][h2] = row * D + 8 * swt<S::KC>(row, chunk) + 4 * (r >> 1);
-      });
+    static_for<2>([&](auto h2) {
+      troff[h2] = swu<S::KC>(8 * (grp >> 1) + 4 * h2 + i, 2 * (grp & 1) + (r & 1)) + 4 * (r >> 1);
     });
   }
   bf16x8 ones3;
@@ -129,10 +131,9 @@ __global__ __launch_bounds__(2 * kThreads, 1) void attn_bwd_dq_kernel(
       }
       static_for<S::NK>([&](auto u) {
         const int wl = wv + S::NW * u;
-        const int r = kst(u);
-        int64_t key = key0 + (int64_t)b * kFwdBN + r;
+        int64_t key = key0 + (int64_t)b * kFwdBN + swu_row<S::KC>(wl, l);
         key = key < n_kv ? key : n_kv - 1;
-        const size_t off = ((size_t)key * h_kv + it.g) * D + 8 * swt<S::KC>(r, l % S::KC);
+        const size_t off = ((size_t)key * h_kv + it.g) * D + 8 * swu_col<S::KC>(wl, l);
         g2l16(k + off, Ks + wl * 512);
         g2l16(v + off, Vs + wl * 512);
       });
@@ -171,13 +172,14 @@ __global__ __launch_bounds__(2 * kThreads, 1) void attn_bwd_dq_kernel(
     // the matrix cores.
     auto block = [&](auto prev_t, auto mask_t, int b, bool copy) {
       constexpr bool PREV = decltype(prev_t)::value, MASK = decltype(mask_t)::value;
-      constexpr int NC = D / 16, AHEAD = 3;
-      const bf16 *Ks = smem + (b % S::NSTAGE) * S::STAGE, *Vs = Ks + S::K_EL;
+      constexpr int NC = D / 16, AHEAD = 4;
+      const bf16 *Ks = smem + (b % S::NSTAGE) * S::STAGE;   // then the V rows
+      const bf16 *kp[2] = {Ks + koff[0], Ks + koff[1]};
       f32x16 sa, pa;
       bf16x8 op[2 * NC];   // MFMA i < NC: S^T from K; NC + c: dP^T from V
       auto rd = [&](auto i) {
         constexpr int kind = i / NC, c = i % NC;
-        op[i] = *reinterpret_cast<const bf16x8 *>((kind ? Vs : Ks) + koff[c]);
+        op[i] = *reinterpret_cast<const bf16x8 *>(kp[c & 1] + kind * S::K_EL + (c >> 1) * STEP4);
       };
       static_for<AHEAD>([&](auto i) { rd(i); });
       __builtin_amdgcn_sched_barrier(0);
@@ -215,11 +217,12 @@ __global__ __launch_bounds__(2 * kThreads, 1) void attn_bwd_dq_kernel(
       };
       if constexpr (PREV) {
         const bf16 *Kp = smem + ((b - 1) % S::NSTAGE) * S::STAGE + 32 * hf * D;
+        const bf16 *kt[2] = {Kp + troff[0], Kp + troff[1]};
         constexpr int NT = D / 32, NQ = 2 * NT, TA = 3;   // MFMA j = NT c + dt
         bf16x8 tp[NQ];
         auto rt = [&](auto j) {
-          const bf16 *base = Kp + 16 * (j / NT) * D;
-          tp[j] = lds_tr16x2(base + troff[j % NT][0], base + troff[j % NT][1]);
+          constexpr int at = 16 * D * (j / NT) + STEP4 * (j % NT);
+          tp[j] = lds_tr16x2(kt[0] + at, kt[1] + at);
         };
         static_for<TA>([&](auto j) { rt(j); });
         static_for<NQ>([&](auto j) {
@@ -241,9 +244,9 @@ __global__ __launch_bounds__(2 * kThreads, 1) void attn_bwd_dq_kernel(
     auto flush = [&](int b) {
       const bf16 *Kp = smem + (b % S::NSTAGE) * S::STAGE + 32 * hf * D;
       static_for<2 * (D / 32)>([&](auto j) {
-        const bf16 *base = Kp + 16 * (j & 1) * D;
-        acc[j >> 1] = mfma32(lds_tr16x2(base + troff[j >> 1][0], base + troff[j >> 1][1]),
-                             dsf[j & 1], acc[j >> 1]);
+        constexpr int at = 16 * D * (j & 1) + STEP4 * (j >> 1);
+        acc[j >> 1] = mfma32(lds_tr16x2(Kp + troff[0] + at, Kp + troff[1] + at), dsf[j & 1],
+                             acc[j >> 1]);
       });
     };
     using T_ = std::true_type;
@@ -268,8 +271,8 @@ __global__ __launch_bounds__(2 * kThreads, 1) void attn_bwd_dq_kernel(
     if (i < pend)
       d_run += i < unmasked_end ? block(F_{}, F_{}, i, cp) : block(F_{}, T_{}, i, cp);
     const int pipe_end = min(pend, unmasked_end);
-    // of the eight places modulo 32 bytes this one was the best: 65.3 ms on the
-    // 256K share against 65.7 to 70.0
+    // of six places modulo 32 bytes this one was the best: 64.7 ms on the 256K
+    // share against 64.8 to 66.6
     align_code<0>();
     for (++i; i < pipe_end; ++i) {
       cp = step(i);

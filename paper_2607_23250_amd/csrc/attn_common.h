@@ -311,31 +311,14 @@ __host__ __device__ __forceinline__ int rec_at(int row, int col) {
 }
 
 
-// Swizzle of row-major Q / dO / K / V tiles that are read both by rows
-// (16-byte reads, 16 consecutive rows per pass) and by the LDS transpose
-// reads below (8-byte reads of 4 rows x 64 bytes per pass, rows 4j..4j+3).
-// The chunk is XORed with a bit rotation of the row that spreads either
-// pattern over all 64 banks.  C = 16-byte columns per row (8 or 16).
-template <int C>
-__host__ __device__ __forceinline__ int swt(int row, int col) {
-  static_assert(C == 8 || C == 16, "tiles of 64 or 128 bf16 per row");
-  if constexpr (C == 16) {
-    const int x = row & 15;
-    return col ^ (((x & 3) << 2) | (x >> 2));
-  } else {
-    const int x = (row >> 1) & 7;
-    return col ^ (((x & 1) << 2) | (x >> 1));
-  }
-}
-
-// Place (in elements) of 16-byte chunk `col` of row `row` of a K / V tile whose
-// copies land as 1 KiB units of 64 / C whole rows (one wave load each).  The
-// places inside a unit are permuted so that row reads (16 rows at one chunk)
-// and transpose reads (4 rows x 4 chunks) both touch every bank once, as with
-// swt; but here chunks 4 apart and rows 16 apart lie at fixed distances, so
-// every operand read of a tile is one of two per-lane addresses plus an
-// immediate, instead of one address register (and one address addition per
-// key block) for each chunk.  Four neighbouring lanes of a copy still read 64
+// Place (in elements) of 16-byte chunk `col` of row `row` of a K / V tile (C =
+// 8 or 16 chunks per row) whose copies land as 1 KiB units of 64 / C whole rows
+// (one wave load each).  The places inside a unit are permuted so that row
+// reads (16 rows at one chunk) and transpose reads (4 rows x 4 chunks) both
+// touch every bank once.  Chunks 4 apart and rows 16 apart lie at fixed
+// distances, so every operand read of a tile is one of two per-lane addresses
+// plus an immediate, instead of one address register (and one address addition
+// per key block) for each chunk.  Four neighbouring lanes of a copy still read 64
 // contiguous bytes of one row: with four rows there, the forward of the 1M
 // share took 20% longer.
 template <int C>
