@@ -67,7 +67,7 @@ def build(verbose: bool = False, jobs: int = 4) -> str:
     cmds, objs = [], []
     for src in CXX_SOURCES:
         obj = os.path.join(OUT_DIR, src + ".o")
-        cmds.append(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", f"-I{INCLUDE}", f"-I{CSRC}",
+        cmds.append(["g++", "-O3", "-std=c++17", "-fPIC", "-Wall", f"-I{INCLUDE}", f"-I{CSRC}",
                      "-c", os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
     for src in HIP_SOURCES:

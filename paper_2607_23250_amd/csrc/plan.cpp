@@ -5,7 +5,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
-#include <numeric>
+#include <utility>
 #include <vector>
 
 #include "errors.h"
@@ -197,43 +197,56 @@ extern "C" int libra_plan(const libra_plan_cfg_t *cfg, const int64_t *lengths,
     }
   }
 
-  // Algorithm 2.
+  // Algorithm 2.  The capacity test V (L_r + f) tau_den <= (tau_den + tau_num) S
+  // is L_r + f <= cap with cap the floor of the quotient (integers, exact).
   i128 S = 0;
   for (const Tile &t : tiles) S += t.cost;
-  const i128 cap_rhs = (i128)(c.tau_den + c.tau_num) * S;   // (1+tau)*S*tau_den
-  const i128 cap_lhs_mul = (i128)c.tau_den * V;
-  std::vector<i64> order(T);
-  std::iota(order.begin(), order.end(), 0);
-  std::sort(order.begin(), order.end(), [&](i64 a, i64 b) {
-    if (tiles[a].cost != tiles[b].cost) return tiles[a].cost > tiles[b].cost;
-    return tiles[a].id < tiles[b].id;
-  });
+  const i128 cap128 = (i128)(c.tau_den + c.tau_num) * S / ((i128)c.tau_den * V);
+  const bool wide = !fits_i64(cap128);   // then compared in 128 bits
+  const i64 cap = wide ? 0 : (i64)cap128;
+  std::vector<std::pair<i64, int32_t>> order((size_t)T);   // (-cost, tile): ids ascend with tiles
+  for (i64 i = 0; i < T; ++i) order[(size_t)i] = {-tiles[(size_t)i].cost, (int32_t)i};
+  std::sort(order.begin(), order.end());
   std::vector<i64> load(V, 0), received(V, 0);
   std::vector<int32_t> assign(T, -1);
   std::vector<i64> delta(V);
-  for (i64 idx : order) {
-    const Tile &t = tiles[idx];
-    bool any_feasible = false;
-    for (i64 r = 0; r < V; ++r) {
-      i128 d = (r == t.home) ? 0 : 2 * (i128)t.vq;
-      for (i64 s = t.s_first; s <= t.s_last; ++s)
-        if (!resident[(size_t)((s * H + t.shard) * V + r)]) d += vg[s];
-      if (!fits_i64(d)) return fail(LIBRA_EOVERFLOW, "communication bytes overflow int64");
-      delta[r] = (i64)d;
-      any_feasible |= cap_lhs_mul * ((i128)load[r] + t.cost) <= cap_rhs;
-    }
-    i64 best = -1;
-    for (i64 r = 0; r < V; ++r) {
-      if (any_feasible) {
-        if (cap_lhs_mul * ((i128)load[r] + t.cost) > cap_rhs) continue;
-        if (best < 0 || delta[r] < delta[best] ||
-            (delta[r] == delta[best] && load[r] < load[best]))
-          best = r;
-      } else {
-        if (best < 0 || load[r] < load[best] ||
-            (load[r] == load[best] && delta[r] < delta[best]))
-          best = r;
+  for (const auto &next : order) {
+    const i64 idx = next.second;
+    const Tile &t = tiles[(size_t)idx];
+    // the bytes that a worker with nothing resident would receive bound them all
+    i128 most = 2 * (i128)t.vq;
+    for (i64 s = t.s_first; s <= t.s_last; ++s) most += vg[s];
+    if (fits_i64(most)) {
+      i64 *d = delta.data();
+      std::fill(delta.begin(), delta.end(), 2 * t.vq);
+      d[t.home] = 0;
+      for (i64 s = t.s_first; s <= t.s_last; ++s) {
+        const uint8_t *res = &resident[(size_t)((s * H + t.shard) * V)];
+        const i64 bytes = vg[s];
+        for (i64 r = 0; r < V; ++r) d[r] += bytes & ((i64)res[r] - 1);
       }
+    } else {
+      for (i64 r = 0; r < V; ++r) {
+        i128 d = (r == t.home) ? 0 : 2 * (i128)t.vq;
+        for (i64 s = t.s_first; s <= t.s_last; ++s)
+          if (!resident[(size_t)((s * H + t.shard) * V + r)]) d += vg[s];
+        if (!fits_i64(d)) return fail(LIBRA_EOVERFLOW, "communication bytes overflow int64");
+        delta[r] = (i64)d;
+      }
+    }
+    // among the workers with room: least (delta, load); with none: least
+    // (load, delta); the lowest worker on ties
+    const i64 room = cap - t.cost;   // cost >= 0
+    i64 best = -1;
+    for (i64 r = 0; r < V; ++r)
+      if ((wide ? (i128)load[r] + t.cost <= cap128 : load[r] <= room) &&
+          (best < 0 || delta[r] < delta[best] ||
+           (delta[r] == delta[best] && load[r] < load[best])))
+        best = r;
+    if (best < 0) {
+      best = 0;
+      for (i64 r = 1; r < V; ++r)
+        if (load[r] < load[best] || (load[r] == load[best] && delta[r] < delta[best])) best = r;
     }
     assign[idx] = (int32_t)best;
     if (!fits_i64((i128)load[best] + t.cost)) return fail(LIBRA_EOVERFLOW, "load overflows");
