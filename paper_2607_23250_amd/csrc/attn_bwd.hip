@@ -1193,7 +1193,7 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
                        BwdPrep{cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, ext, gmask, items,
                                L.max_items, cus, reinterpret_cast<BwdSplit *>(ws + L.bsplits)},
                        FwdPrep{cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, qitems, L.max_qitems, 0,
-                               cus, max_parts, 1, splits});
+                               cus, cus, max_parts, 1, splits});
     // K and V rows: at least eight for a wave (every workgroup that finds a new
     // maximum posts an atomic on the same two slots: 2048 of them took 24 us on
     // 4096 rows)

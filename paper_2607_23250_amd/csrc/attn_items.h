@@ -69,7 +69,10 @@ struct FwdPrep {
   int32_t *hdr;
   FwdItem *items;
   int64_t max_items;
-  int count_bad, grid, max_parts, idle_only;
+  int count_bad;
+  int grid;        // workgroups that run the items
+  int split_grid;  // workgroups that the split rule counts
+  int max_parts, idle_only;
   FwdSplit *splits;
 };
 struct FwdPrepLds {
@@ -82,7 +85,7 @@ struct FwdPrepLds {
 __device__ __forceinline__ void prep_fwd(const FwdPrep &a, FwdPrepLds &lds) {
   const int64_t n = a.n, T = a.T, n_q = a.n_q, n_kv = a.n_kv;
   const libra_tile_t *tiles = a.tiles;
-  const int h_q = a.h_q, h_kv = a.h_kv, grid = a.grid, max_parts = a.max_parts;
+  const int h_q = a.h_q, h_kv = a.h_kv, grid = a.split_grid, max_parts = a.max_parts;
   int32_t *hdr = a.hdr;
   auto &s_wmax = lds.wmax, &s_items = lds.items, &s_work = lds.work, &s_parts = lds.parts,
        &s_pairs = lds.pairs;
@@ -194,7 +197,7 @@ __device__ __forceinline__ void prep_fwd(const FwdPrep &a, FwdPrepLds &lds) {
       }
     });
   };
-  build_queues<FwdItem>(each, lds.hist, lds.part, hdr, kFwdQ, a.items, a.max_items, grid);
+  build_queues<FwdItem>(each, lds.hist, lds.part, hdr, kFwdQ, a.items, a.max_items, a.grid);
   __syncthreads();
   if (tid == 0) {
     hdr[kFwdSplits] = s_nsplit;
