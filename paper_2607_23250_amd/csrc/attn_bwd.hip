@@ -14,7 +14,7 @@
 //     queries on M (lane = key), exactly the operand layout that dV^T = dO^T P
 //     and dK^T = Q^T dS need; the dO^T / Q^T operands come from the same LDS
 //     tiles through the LDS transpose reads.  LSE and D enter the S and dP
-//     products as one extra k-block (see bwd_pre_kernel), so the VALU only
+//     products as one extra k-block (see pre_pass), so the VALU only
 //     exponentiates and multiplies.  A step's Q, dO and extra operands are two
 //     contiguous records that the pre-pass lays out as the LDS stage wants
 //     them; steps are staged in a 4-deep LDS ring, three ahead of the one
@@ -565,14 +565,14 @@ struct KvShape {
 struct StepIter {
   const libra_tile_t *tiles;
   int64_t T, n_q, n_kv, key0, p0, p1;   // rows at positions [p0, p1)
-  int h_q, g, G, kloc0, rbytes;   // rbytes: of a record
+  int h_q, g, G, kloc0, rkib;   // rkib: KiB of a record
   // fragment
   int64_t t;                // tile index
   int nm, lo0, hin, qb0;    // blocks; lo of block 0; hi of the last block; q_loc of its row 0
   int h0, h1;
   // position
   int mi, h;
-  int64_t rec;              // byte offset of the record of (block, h)
+  int64_t rec;              // offset of the record of (block, h), in KiB
   bool valid;
 
   __device__ bool seek() {
@@ -598,7 +598,7 @@ struct StepIter {
       qb0 = (int)(qla - (fra - row0));
       mi = 0;
       h = h0;
-      rec = (mf * h_q + h0) * rbytes;
+      rec = (mf * h_q + h0) * rkib;
       return true;
     }
     return false;
@@ -608,10 +608,10 @@ struct StepIter {
   // step of an odd head count
   __device__ void next() {
     if ((h += 2) < h1) {
-      rec += 2 * rbytes;
+      rec += 2 * rkib;
       return;
     }
-    rec += (int64_t)((h_q - (h - 2 - h0)) * rbytes);   // back by the heads advanced within this block
+    rec += (int64_t)((h_q - (h - 2 - h0)) * rkib);   // back by the heads advanced within this block
     h = h0;
     if (++mi < nm) return;
     ++t;
@@ -934,7 +934,7 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
     // in ring stage j (lo | hi << 8 | two << 16, and the q_loc of the block's
     // row 0) waits in lane j of desc / desc_qb.
     StepIter iss{tiles, T, n_q, n_kv, key0, key0 + item.r0,
-                 key0 + (item.r1 < len ? item.r1 : len), h_q, g, G, kloc0, 2 * S::HEAD_EL};
+                 key0 + (item.r1 < len ? item.r1 : len), h_q, g, G, kloc0, 2 * S::HEAD_EL / 1024};
     iss.start();
     int desc = 0, desc_qb = 0;
     int issued = 0, computed = 0;
@@ -946,7 +946,7 @@ __global__ __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 
       const int sg = posted & (S::NSTAGE - 1);
       cp_dst = lds_addr(smem + sg * S::STAGE_EL) + bytes * w;
       if (!iss.valid) return;
-      cp_src = reinterpret_cast<const char *>(rec) + uniform64(iss.rec) + bytes * w;
+      cp_src = reinterpret_cast<const char *>(rec) + (uniform64(iss.rec) << 10) + bytes * w;
       if (l == sg) {
         desc = iss.lo() | iss.hi() << 8 | (iss.two() ? 1 << 16 : 0);
         desc_qb = iss.qb();

@@ -297,7 +297,7 @@ __device__ __forceinline__ float row_sum2(float x) {
 // query rows and one query head, contiguous and already in the order of the
 // LDS stage: the scaled fp16 copies of Q and of dO (32 x D each, placed by
 // rec_at), then two MFMA A-operands of 64 lanes x 8 fp16 (-LSE / scale, then
-// -D; see bwd_pre_kernel).  Record (block m, head h) is number m * h_q + h.
+// -D; see pre_pass).  Record (block m, head h) is number m * h_q + h.
 constexpr int kAugEl = 2 * 64 * 8;
 __host__ __device__ constexpr int rec_els(int d) { return 2 * kRows * d + kAugEl; }
 // Place (in elements) of 16-byte chunk `col` of row `row` in a record's Q or
@@ -529,20 +529,6 @@ __device__ __forceinline__ void wait_vm_known() { __builtin_amdgcn_s_waitcnt(0x0
 // Wait for this wave's outstanding global loads (including global -> LDS).
 __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Scheduling hint for a run of N MFMAs that each consume one 16-byte LDS
-// read: issue AHEAD reads first, then alternate one MFMA with one read, so
-// that every read is in flight while earlier MFMAs execute.
-template <int N, int AHEAD>
-__device__ __forceinline__ void sched_pipeline() {
-  __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);   // DS reads
-#pragma unroll
-  for (int i = 0; i < N - AHEAD; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // MFMA
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // DS read
-  }
-  __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
-}
-
 // x as hi + mid + lo, three bf16 values in elements 0..2 of r, the rest zero
 // (exact to about 2^-24 |x|).  Against a k-block of ones in k = 0, 1, 2 an
 // MFMA adds x itself to every accumulator of the row (or column).
@@ -587,20 +573,6 @@ template <int N>
 __device__ __forceinline__ void wait_vm_n() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-// Wait until at most k * L vector-memory operations are outstanding
-// (k in [0, KMAX]; larger k wait for KMAX * L).
-template <int L, int KMAX>
-__device__ __forceinline__ void wait_stages(int k) {
-  bool done = false;
-  static_for<KMAX>([&](auto i) {
-    if (!done && k == int(i)) {
-      wait_vm_n<int(i) * L>();
-      done = true;
-    }
-  });
-  if (!done) wait_vm_n<KMAX * L>();
-}
-
 // A zero accumulator produced by an MFMA: in kernels whose MFMAs write
 // AGPRs this keeps long-lived accumulators in AGPRs from their first
 // definition (a VALU zero-fill would be a VGPR definition and make the

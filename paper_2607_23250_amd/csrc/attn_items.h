@@ -47,9 +47,9 @@ __device__ void for_each_fwd_item_in(const libra_tile_t &t, int64_t wa, int64_t 
 // outside the buffers are skipped, and counted in hdr[kBadTiles] when
 // `count_bad` is set (the backward counts them in its own preparation pass).
 //
-// Split K: when there are fewer than two items per workgroup of the `grid`
-// that runs them (few rows and heads against long samples), and with
-// `idle_only` only when whole rounds of `grid` items would leave more than a
+// Split K: when there are fewer than two items per workgroup of `split_grid`
+// (few rows and heads against long samples), and with
+// `idle_only` only when whole rounds of that many items would leave more than a
 // tenth of the workgroups idle, the key blocks that all rows of an item
 // attend in full (below its first row's block kd) are cut into ranges of C
 // blocks, about four items per workgroup in all;
@@ -154,7 +154,7 @@ __device__ __forceinline__ void prep_fwd(const FwdPrep &a, FwdPrepLds &lds) {
     });
     __syncthreads();
     const unsigned long long n_items = s_items, work = s_work, gr = (unsigned long long)grid;
-    // rounds of `grid` items fill less than 90% of the workgroups
+    // rounds of that many items fill less than 90% of the workgroups
     const bool idle = n_items * 10 < (n_items + gr - 1) / gr * gr * 9;
     if (n_items > 0 && n_items < 2 * gr && (idle || !a.idle_only)) {
       long long c = (long long)((work + 4ull * grid - 1) / (4ull * grid));

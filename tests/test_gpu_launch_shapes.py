@@ -52,12 +52,13 @@ def _check(lengths, tiles, h_q, h_kv, d, seed=5):
     assert not to_np(dk)[:, other].any() and not to_np(dv)[:, other].any()
 
 
-@pytest.mark.parametrize("n_items", (1, 32, 33, 64, 65, 700))
+@pytest.mark.parametrize("n_items", (1, 32, 33, 64, 65, 700, 1025, 2048))
 def test_one_queue_holds_every_item(n_items):
     """One of eight heads (no grouping): all items lie in one queue.  With more
     of them than its own workgroups (64 of the forward, 32 of the backward) the
     others have to come from the seven empty queues; with fewer, every
-    workgroup has to find its way out."""
+    workgroup has to find its way out.  From 1025 samples on their extents, and
+    from 2048 on their offsets, stay in memory during the preparation."""
     lengths = [int(x) for x in np.random.default_rng(n_items).integers(1, 60, n_items)]
     n = sum(lengths)
     say(f"[one queue] {n_items} items of one head, {n} rows")
