@@ -159,9 +159,10 @@ def libra_plan(lengths: Sequence[int], pack_tokens: Sequence[int], *, block_toke
         nqr = len(qr) // 2
     n_tiles = ctypes.c_int64(0)
     args = (ctypes.byref(cfg), _ptr(lengths), len(lengths), _ptr(cu), _ptr(pack_cu), _ptr(qr), nqr)
-    if qr is None and block_tokens > 0 and head_shards > 0 and pack_cu[-1] <= _PLAN_ONE_CALL:
+    total = int(pack_cu[-1])
+    if qr is None and 0 < block_tokens and 0 < head_shards and 0 < total <= _PLAN_ONE_CALL:
         # every block of every pack makes head_shards tiles: no call to count them
-        count = int((-(-np.diff(pack_cu) // block_tokens)).sum()) * head_shards
+        count = head_shards * sum(-(-int(t) // block_tokens) for t in pack_tokens)
         count = min(max(count, 0), _PLAN_ONE_CALL)
     else:
         _check(L.libra_plan(*args, None, 0, ctypes.byref(n_tiles), None, None), "libra_plan")
@@ -171,7 +172,8 @@ def libra_plan(lengths: Sequence[int], pack_tokens: Sequence[int], *, block_toke
     recv = np.zeros(len(pack_tokens) * cp, dtype=np.int64) if with_bytes else None
     _check(L.libra_plan(*args, _ptr(tiles), len(tiles), ctypes.byref(n_tiles), _ptr(loads),
                         _ptr(recv)), "libra_plan")
-    tiles = tiles[:n_tiles.value]
+    if n_tiles.value != count:
+        tiles = tiles[:n_tiles.value]
     return (tiles, loads, recv) if with_bytes else (tiles, loads)
 
 
