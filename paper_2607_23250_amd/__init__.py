@@ -112,9 +112,9 @@ def _ptr(a: np.ndarray):
     return a.ctypes.data_as(ctypes.c_void_p) if a is not None else None
 
 
-# Planner calls of up to this many tokens size their tile array without a call
-# that counts the tiles.
-_PLAN_ONE_CALL = 1 << 26
+# Plans of up to this many tiles, on up to this many workers, size their arrays
+# without a call that counts the tiles; a refused plan allocates no more.
+_PLAN_ONE_CALL = 1 << 20
 
 
 def _int64s(values) -> np.ndarray:
@@ -159,12 +159,12 @@ def libra_plan(lengths: Sequence[int], pack_tokens: Sequence[int], *, block_toke
         nqr = len(qr) // 2
     n_tiles = ctypes.c_int64(0)
     args = (ctypes.byref(cfg), _ptr(lengths), len(lengths), _ptr(cu), _ptr(pack_cu), _ptr(qr), nqr)
-    total = int(pack_cu[-1])
-    if qr is None and 0 < block_tokens and 0 < head_shards and 0 < total <= _PLAN_ONE_CALL:
-        # every block of every pack makes head_shards tiles: no call to count them
-        count = head_shards * sum(-(-int(t) // block_tokens) for t in pack_tokens)
-        count = min(max(count, 0), _PLAN_ONE_CALL)
-    else:
+    count = 0
+    if qr is None and cfg.block_tokens > 0 and 0 < cp * len(pack_tokens) <= _PLAN_ONE_CALL:
+        # every block of every pack makes head_shards tiles (of the sizes as the
+        # library sees them): no call to count them
+        count = cfg.head_shards * sum(-(-int(t) // cfg.block_tokens) for t in pack_tokens)
+    if not 0 < count <= _PLAN_ONE_CALL:
         _check(L.libra_plan(*args, None, 0, ctypes.byref(n_tiles), None, None), "libra_plan")
         count = n_tiles.value
     tiles = np.zeros(count, dtype=TILE_DTYPE)

@@ -35,6 +35,36 @@ def test_tile_count_without_a_counting_call(block):
     assert len(a[0]) and _same(a, b)
 
 
+@pytest.mark.parametrize("limit", (0, 1, 767, 768, 1 << 20))
+def test_more_tiles_than_one_call_sizes(limit, monkeypatch):
+    """384 one-token blocks in two shards: above the bound the library counts
+    them, and the plan is the same."""
+    lengths = [100, 1, 155, 60, 68]
+    want = _plan(lengths, block_tokens=1)
+    assert len(want[0]) == 768
+    monkeypatch.setattr(pl, "_PLAN_ONE_CALL", limit)
+    assert _same(want, _plan(lengths, block_tokens=1))
+
+
+def test_block_tokens_as_the_library_sees_them():
+    """The library's fields have 32 bits; the tile count follows them."""
+    lengths = [100, 1, 155, 60, 68]
+    assert _same(_plan(lengths, block_tokens=48), _plan(lengths, block_tokens=48 + (1 << 32)))
+
+
+@pytest.mark.parametrize("kw", (dict(cp=-1), dict(cp=0), dict(cp=1 << 30),
+                                dict(cp=1 << 30, block_tokens=1), dict(head_shards=1 << 30)))
+def test_refused_before_anything_is_allocated(kw, monkeypatch):
+    def zeros(shape, *a, **k):
+        assert int(np.prod(shape)) < 1 << 16, "array for a refused plan"
+        return real(shape, *a, **k)
+    real = np.zeros
+    monkeypatch.setattr(pl.np, "zeros", zeros)
+    with pytest.raises(pl.LibraError) as e:
+        _plan([100, 1, 155, 60, 68], **kw)
+    assert e.value.code == pl.LIBRA_EINVAL
+
+
 @pytest.mark.parametrize("lengths,kw", [([], {}), ([384], {}), ([256, 128], dict(block_tokens=0)),
                                         ([256, 128], dict(head_shards=3)), ([256, 0, 128], {}),
                                         ([256, 127], {})])
