@@ -218,7 +218,7 @@ int libra_attn_skipped_tiles(const void *workspace, int32_t *count, void *stream
  * split K (its partial slots would not fit), so its results equal
  * libra_attn_fwd's whenever that call splits no item; the work items live in
  * a device array built into the library, of LIBRA_FWD_NOALLOC_MAX_WORKSPACE
- * bytes, one per device, held until the process ends.  The call allocates
+ * bytes and a small header, one per device, held until the process ends.  The call allocates
  * nothing and frees nothing (its first call on a device looks up that
  * device's array).
  *   Sizes whose work-item list (48 bytes per item, bounded from the sizes as

@@ -16,9 +16,11 @@ using namespace libra;
 // Device scratch of libra_attn_fwd_noalloc: the forward's work-item
 // workspace, one copy per device (each GPU the library runs on holds it until
 // the process ends).  In host code `scratch` names a host-side stand-in: its
-// device address comes from hipGetSymbolAddress, per device (scratch_ptr).
-constexpr size_t kNoAllocScratchBytes = size_t(16) << 20;
-static_assert(kNoAllocScratchBytes == LIBRA_FWD_NOALLOC_MAX_WORKSPACE, "documented limit");
+// device address comes from hipGetSymbolAddress, per device (scratch_ptr).  The
+// documented limit counts the list with 256 bytes before it, whatever the
+// header takes.
+constexpr size_t kNoAllocListBytes = LIBRA_FWD_NOALLOC_MAX_WORKSPACE - 256;
+constexpr size_t kNoAllocScratchBytes = kHdrBytes + kNoAllocListBytes;
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {
@@ -172,10 +174,10 @@ extern "C" int libra_attn_fwd_noalloc(const void *q, const void *k, const void *
   // no split K here: its partial slots would not fit the scratch
   const FwdLayout L =
       fwd_layout(num_tiles, num_samples, n_q_rows, n_kv_rows, h_q, h_kv, head_dim, false);
-  if (L.total > kNoAllocScratchBytes)
-    return fail(LIBRA_ENOSPC, "these sizes need %zu bytes of workspace, more than the %zu of "
-                "the built-in scratch; use libra_attn_fwd with a workspace",
-                L.total, kNoAllocScratchBytes);
+  if (L.total - L.items > kNoAllocListBytes)
+    return fail(LIBRA_ENOSPC, "these sizes need a work-item list of %zu bytes, more than the %zu "
+                "of the built-in scratch; use libra_attn_fwd with a workspace",
+                L.total - L.items, kNoAllocListBytes);
   void *ws = nullptr;
   if (int rc = scratch_ptr(&ws)) return rc;
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.f / std::sqrt((float)head_dim);

@@ -1126,7 +1126,7 @@ BwdLayout bwd_layout(int64_t T, int64_t n, int64_t n_q, int64_t n_kv, int h_q, i
   L.max_qitems = fwd_max_items(T, n, n_q, h_q, h_kv);
   L.nq_pad = (n_q + kRows - 1) / kRows * kRows;
   L.hdr = 0;
-  L.ext = align256b(kHdrSlots * sizeof(int32_t));
+  L.ext = kHdrBytes;
   L.gmask = align256b(L.ext + (size_t)n * sizeof(int32_t));
   L.items = align256b(L.gmask + (size_t)n * sizeof(unsigned long long));
   L.qitems = align256b(L.items + (size_t)L.max_items * sizeof(BwdItem));

@@ -39,9 +39,9 @@ constexpr int kXcds = 8;
 constexpr int kQBuckets = 1024;      // cost buckets per queue
 constexpr int kPrepThreads = 1024;
 
-// Workspace header (int32 slots).  A queue set at `base` keeps the queue
-// heads at [base, base+8), item counts at [base+8, base+16) and segment
-// starts at [base+16, base+24).
+// Workspace header (int32 slots).  A queue set at `base` keeps the item counts at
+// [base+8, base+16) and segment starts at [base+16, base+24); its queue heads
+// are at head_slot(base, queue).
 enum HdrSlot {
   kBadTiles = 4,   // tiles skipped because they were out of range (+1 on item overflow)
   kOddHeads = 5,   // backward: some tile covers an odd number of a KV group's heads
@@ -50,8 +50,20 @@ enum HdrSlot {
   kBwdQ = 32,      // dK/dV work items
   kMaxAbs = 56,    // backward: max |x| (fp32 bits) of Q, dO, K, V in slots 56..59
   kFwdSplits = 60, // forward: split items (FwdSplit records), then partial slots used (61)
-  kHdrSlots = 64
+  kFwdHeads = 64,  // queue heads of the forward / dQ work items
+  kHdrSlots = kFwdHeads + kXcds * 32
 };
+constexpr size_t kHdrBytes = (kHdrSlots * sizeof(int32_t) + 255) / 256 * 256;
+// Head of queue x of the set at `base`.  Each head of the forward / dQ set has a
+// 128-byte line of its own: atomics of many workgroups on one line are served one
+// after another, about 50 ns each, so with all heads on one line a call of many
+// short items took as long as its items' atomics (65536 samples of 16 rows,
+// 131072 forward items, 8 / 2 heads, d = 64: 8.32 ms, and 1.62 with a line per
+// head; 16K tokens in 5 samples, 8 / 4 heads, d = 64: 214 and 181 us).  The dK / dV
+// items are longer, and the heads of their set share a line.
+__host__ __device__ constexpr int head_slot(int base, int x) {
+  return base == kFwdQ ? kFwdHeads + 32 * x : base + x;
+}
 static_assert(kBadTiles * 4 == LIBRA_WS_SKIPPED_OFFSET, "documented offset of the skip count");
 
 // Compile-time loop: f(std::integral_constant<int, i>{}) for i in [0, N).  Register
@@ -115,7 +127,7 @@ __device__ void build_queues(Each &&each, int32_t *hist, int32_t *part, int32_t 
     const int32_t start = pos;
     const int32_t end = part[tid + threads_per_queue - 1];
     const int32_t lim = (int32_t)(max_items < INT32_MAX ? max_items : INT32_MAX);
-    hdr[base + x] = (grid - x + kXcds - 1) / kXcds;
+    hdr[head_slot(base, x)] = (grid - x + kXcds - 1) / kXcds;
     hdr[base + kXcds + x] = (end < lim ? end : lim) - (start < lim ? start : lim);
     hdr[base + 2 * kXcds + x] = start;
     if (x == kXcds - 1 && end > lim) atomicAdd(&hdr[kBadTiles], 1);
@@ -151,11 +163,10 @@ __device__ __forceinline__ int32_t ld_agent(const int32_t *p) {
 // workgroup's own queue, and `state` says whether it may still hold items.  The
 // own queue is asked with an atomic; the others only when a look at all eight
 // heads (one lane each, agent scope, one round trip) finds items left.  Asking
-// every queue with an atomic before giving up cost 8 atomics per workgroup on
-// one cache line across the XCDs, which serve them at about 66 ns each: 270 us
-// at the end of a launch of 512 workgroups (a forward of 512 tokens took
-// 313 us, now 30).  Every failed atomic leaves its queue's head at or past the
-// end, so the loop ends after at most nine.
+// every queue with an atomic before giving up cost 8 atomics per workgroup at
+// the end of a launch, 270 us for 512 workgroups when the heads shared a line (a
+// forward of 512 tokens took 313 us, now 23).  Every failed atomic leaves its
+// queue's head at or past the end, so the loop ends after at most nine.
 enum TakeState { kTakeFirst, kTakeOwn, kTakeOther };
 __device__ __forceinline__ int take_item(int32_t *hdr, int base, int q, int &state) {
   int32_t *set = hdr + base;
@@ -171,15 +182,16 @@ __device__ __forceinline__ int take_item(int32_t *hdr, int base, int q, int &sta
   }
   for (int x = q;;) {
     if (state == kTakeOther) {
-      const bool some = lane < kXcds && ld_agent(&set[lane & (kXcds - 1)]) <
-                                            set[kXcds + (lane & (kXcds - 1))];
+      const bool some = lane < kXcds &&
+                        ld_agent(&set[head_slot(base, lane & (kXcds - 1)) - base]) <
+                            set[kXcds + (lane & (kXcds - 1))];
       const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(some);
       if (m == 0) return -1;
       // the nearest queue at or after the own one that holds items
       x = (q + __builtin_ctz((m | m << kXcds) >> q)) & (kXcds - 1);
     }
     int got = 0;
-    if (lane == 0) got = atomicAdd(&set[x], 1);
+    if (lane == 0) got = atomicAdd(&set[head_slot(base, x) - base], 1);
     got = __builtin_amdgcn_readfirstlane(got);
     if (got < set[kXcds + x]) return set[2 * kXcds + x] + got;
     state = kTakeOther;

@@ -383,7 +383,7 @@ FwdLayout fwd_layout(int64_t T, int64_t n, int64_t n_q, int64_t n_kv, int h_q, i
   FwdLayout L;
   L.max_items = fwd_max_items(T, n, n_q, h_q, h_kv);
   L.hdr = 0;
-  L.items = align256(kHdrSlots * sizeof(int32_t));
+  L.items = kHdrBytes;
   L.splits = align256(L.items + (size_t)L.max_items * sizeof(FwdItem));
   L.max_parts = split ? kFwdSplitSlots : 0;
   // a split item has at least two parts

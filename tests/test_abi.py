@@ -5,6 +5,9 @@ import glob
 import os
 import re
 
+import pytest
+import torch
+
 import paper_2607_23250_amd as pl
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -106,3 +109,24 @@ def test_noalloc_forward_rejects_oversize_on_the_host():
     rc = L.libra_attn_fwd_noalloc(dummy, dummy, dummy, dummy, 4, dummy, 16, 4096, 4096, 8, 2, 96,
                                   C.c_float(0.0), dummy, dummy, None)
     assert rc == pl.LIBRA_EUNSUPPORTED
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="an accepted call would be enqueued")
+def test_noalloc_forward_limit_counts_the_work_item_list():
+    """The limit is 16 MiB of 48-byte items and 256 bytes, independent of the
+    header: the largest accepted tile count stays accepted (and ends at the
+    device lookup here, where there is no GPU)."""
+    import ctypes as C
+    L = pl.lib()
+    dummy = C.c_void_p(256)
+    n, rows, h_q, h_kv, d = 4, 4096, 8, 2, 128
+
+    def items(T):
+        return rows * h_q // 64 + (T + h_q * n) * (h_kv + h_q // 4 + 1) + 1 + 3072
+
+    T = 1
+    while (items(T + 1) * 48 + 255) // 256 * 256 <= pl.LIBRA_FWD_NOALLOC_MAX_WORKSPACE - 256:
+        T += 1
+    rc = [L.libra_attn_fwd_noalloc(dummy, dummy, dummy, dummy, n, dummy, t, rows, rows, h_q, h_kv,
+                                   d, C.c_float(0.0), dummy, dummy, None) for t in (T, T + 1)]
+    assert rc == [pl.LIBRA_EHIP, pl.LIBRA_ENOSPC]
