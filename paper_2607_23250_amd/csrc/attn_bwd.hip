@@ -147,11 +147,16 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
   if (odd) atomicOr(&hdr[kOddHeads], 1);
   fence();
   // Samples of more than kCoopItems items are enumerated by the whole
-  // workgroup, the others by one wave each; if the list of long samples
-  // overflows, every sample goes to a wave.  Both enumerations below see the
-  // same items.  (One thread per sample took 82 us on a 32K pack, whose 2,100
-  // items lie in 9 samples.)
+  // workgroup (if the list of them overflows, each by a wave).  The others go to
+  // the waves in groups of up to 64 that one load looks up, a sample to a lane;
+  // a sample of no more items than its group has samples is enumerated by its
+  // lane, the rest of the group one after another by the wave.  Every
+  // enumeration sees the same items.  (One thread per sample took 82 us on a
+  // 32K pack, whose 2,100 items lie in 9 samples; one wave per sample, each with
+  // a lookup of its own, 8.0 ms on 65536 samples of one key block and 2 KV heads,
+  // where groups take less than the dQ list beside them, 0.76.)
   constexpr int kCoopItems = 1024;
+  const int group = (int)max((int64_t)1, min((int64_t)64, n / (kPrepThreads / 64)));
   auto blocks_of = [&](int32_t e) { return (e + kBwdBK - 1) / kBwdBK; };
   for (int64_t j = tid; j < n; j += kPrepThreads) {
     const int32_t e = ext_of(j);
@@ -172,12 +177,22 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
   };
   // every whole item once: f(item, row blocks, queue)
   auto whole = [&](auto &&f) {
-    for (int64_t j = tid >> 6; j < n; j += kPrepThreads / 64) {
-      const int32_t e = ext_of(j);
+    for (int64_t j0 = (int64_t)(tid >> 6) * group; j0 < n; j0 += kPrepThreads / 64 * group) {
+      const int l = tid & 63;
+      const bool in = l < group && j0 + l < n;
+      const int32_t e = in ? ext_of(j0 + l) : 0;
+      const unsigned long long mk = in ? gmask_of(j0 + l) : 0;
       const int count = blocks_of(e) * h_kv;
-      if (coop && count > kCoopItems) continue;
-      const unsigned long long mk = gmask_of(j);
-      for (int i = tid & 63; i < count; i += 64) emit(f, j, e, mk, i);
+      if (count <= group)
+        for (int i = 0; i < count; ++i) emit(f, j0 + l, e, mk, i);
+      unsigned long long wide =
+          __builtin_amdgcn_ballot_w64(count > group && !(coop && count > kCoopItems));
+      for (; wide; wide &= wide - 1) {
+        const int s = __builtin_ctzll(wide);
+        const int32_t es = __shfl(e, s);
+        const unsigned long long ms = __shfl(mk, s);
+        for (int i = l; i < blocks_of(es) * h_kv; i += 64) emit(f, j0 + s, es, ms, i);
+      }
     }
     if (!coop) return;
     for (int k = 0; k < lds.n_long; ++k) {
