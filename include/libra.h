@@ -271,9 +271,9 @@ int libra_attn_fwd_noalloc(const void *q, const void *k, const void *v,
  * Split rows: the dK / dV products cut their work items (128 keys of a KV head
  * against all rows that attend them) into row ranges when the longest item
  * would take a quarter longer than an even spread of the call's work (few
- * samples and KV heads).  Their fp32 partial sums are added in row order, so
- * the result is the same up to the order of fp32 additions, and the same from
- * one call to the next.
+ * samples and KV heads), counting the rows that the tiles cover.  Their fp32
+ * partial sums are added in row order, so the result is the same up to the
+ * order of fp32 additions, and the same from one call to the next.
  */
 int libra_attn_bwd(const void *q, const void *k, const void *v, const void *o, const float *lse,
                    const void *dout, const int64_t *cu_seqlens, int64_t num_samples,

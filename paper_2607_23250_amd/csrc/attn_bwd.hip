@@ -79,9 +79,11 @@ struct BwdPrep {
   int64_t max_items;
   int grid;
   BwdSplit *splits;
+  int32_t *cov, *cov_sum;   // per key block and KV head (see prep_bwd)
 };
 constexpr int kExtLds = 1024;   // samples whose extents and head sets are kept in LDS
 constexpr int kMaxLong = 256;
+constexpr int kPlaces = 2048;   // (key block, KV head) pairs whose covered rows are counted in LDS
 struct BwdPrepLds {
   int32_t hist[kXcds * kQBuckets];
   int32_t part[kPrepThreads];
@@ -89,9 +91,12 @@ struct BwdPrepLds {
   unsigned long long gmask[kExtLds];
   int32_t ext[kExtLds];
   int32_t longs[kMaxLong];
-  int32_t n_long, longest, chunk, nslot, nsplit;
-  unsigned long long work, parts;
+  int32_t cov_sum[kPlaces];
+  uint16_t cuts[kPlaces], at[kExtLds];   // at: first place of a sample, in key blocks
+  int32_t n_long, nslot, nsplit, tile_rows, taken, longest[2], block;
+  unsigned long long covered, reached, work[2];
 };
+static_assert(kPlaces <= kXcds * kQBuckets, "the counts take the place of the histogram");
 static_assert(sizeof(BwdPrepLds) <= 80 * 1024, "two preparation workgroups fit a CU");
 
 __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
@@ -111,14 +116,23 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
     __syncthreads();
   };
   auto ext_of = [&](int64_t j) { return in_lds ? lds.ext[j] : ld_agent(&a.ext[j]); };
+  // Atomics of all lanes on one counter in LDS: at an address that the compiler takes
+  // for a lane's own.  Where it sees that there is one, it makes them a loop over
+  // the lanes, about 1 us.
+  auto at0 = [&](auto *p) {
+    int z = 0;
+    asm volatile("" : "+v"(z));
+    return p + z;
+  };
   auto gmask_of = [&](int64_t j) { return in_lds ? lds.gmask[j] : ld_agent(&a.gmask[j]); };
   for (int64_t j = tid; j < n; j += kPrepThreads) {
     __hip_atomic_store(&ext[j], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&gmask[j], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (tid == 0) {
-    lds.n_long = lds.longest = lds.chunk = lds.nslot = lds.nsplit = 0;
-    lds.work = 0;
+    lds.n_long = lds.nslot = lds.nsplit = lds.tile_rows = lds.taken = 0;
+    lds.covered = lds.reached = lds.work[0] = lds.work[1] = 0;
+    lds.longest[0] = lds.longest[1] = lds.block = 0;
   }
   if (tid < 6) {
     // the skipped-tile count (counted here for the backward), the odd-heads
@@ -128,20 +142,30 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
   }
   __threadfence();
   __syncthreads();
-  int bad = 0;
+  int bad = 0, tile_rows = 0;
   bool odd = false;
+  unsigned long long covered = 0;   // (row, head) pairs
   for (int64_t t = tid; t < T; t += kPrepThreads) {
     const libra_tile_t tl = a.tiles[t];
     if (!tile_ok(tl, n_q, n_kv, h_q)) {
       ++bad;
       continue;
     }
+    tile_rows = max(tile_rows, (int)(tl.q_end - tl.q_begin));
     const unsigned long long bits = group_bits(tl.head_begin, tl.head_end, G, odd);
     for (int64_t j = upper_bound64(cu, n, tl.q_begin) - 1; j < n && cu[j] < tl.q_end; ++j) {
       const int64_t pe = tl.q_end < cu[j + 1] ? tl.q_end : cu[j + 1];
+      const int64_t pb = tl.q_begin > cu[j] ? tl.q_begin : cu[j];
       atomicMax(&ext[j], (int32_t)(pe - cu[j]));
       atomicOr(&gmask[j], bits);
+      if (pb < pe)
+        covered += (unsigned long long)(unsigned)(pe - pb) *
+                   (unsigned)(tl.head_end - tl.head_begin);
     }
+  }
+  if (covered) {
+    atomicAdd(at0(&lds.covered), covered);
+    atomicMax(at0(&lds.tile_rows), tile_rows);
   }
   if (bad) atomicAdd(&hdr[kBadTiles], bad);
   if (odd) atomicOr(&hdr[kOddHeads], 1);
@@ -158,110 +182,248 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
   constexpr int kCoopItems = 1024;
   const int group = (int)max((int64_t)1, min((int64_t)64, n / (kPrepThreads / 64)));
   auto blocks_of = [&](int32_t e) { return (e + kBwdBK - 1) / kBwdBK; };
+  unsigned long long reached = 0;   // (row, head) pairs up to the extents
   for (int64_t j = tid; j < n; j += kPrepThreads) {
     const int32_t e = ext_of(j);
-    if (in_lds) a.ext[j] = e;   // for the passes over K and V
+    if (in_lds) {
+      a.ext[j] = e;   // for the passes over K and V
+      lds.at[j] = (uint16_t)atomicAdd(at0(&lds.taken), blocks_of(e));
+    }
+    if (e) reached += (unsigned long long)e * (unsigned)(G * __builtin_popcountll(gmask_of(j)));
     if ((int64_t)blocks_of(e) * h_kv > kCoopItems) {
       const int32_t slot = atomicAdd(&lds.n_long, 1);
       if (slot < kMaxLong) lds.longs[slot] = (int32_t)j;
     }
   }
+  if (reached) atomicAdd(at0(&lds.reached), reached);
+  for (int i = tid; i < kPlaces; i += kPrepThreads) lds.hist[i] = 0;
   __syncthreads();
   const bool coop = lds.n_long <= kMaxLong;
   // item i of sample j: key block i / h_kv of KV head i % h_kv
   auto emit = [&](auto &&f, int64_t j, int32_t e, unsigned long long mk, int i) {
     const int kb = i / h_kv, g = i - kb * h_kv;
     if (mk >> g & 1ull)
-      f(BwdItem{(int32_t)j, kb, g, -1, 0, INT32_MAX, 0, 0}, (e - kb * kBwdBK + kRows - 1) / kRows,
-        (g * R + kb % R) % kXcds);
+      f(BwdItem{(int32_t)j, kb, g, -1, 0, INT32_MAX, 0, 0}, e, (g * R + kb % R) % kXcds);
   };
-  // every whole item once: f(item, row blocks, queue)
+  // every whole item once: f(item, extent of its sample, queue)
   auto whole = [&](auto &&f) {
-    for (int64_t j0 = (int64_t)(tid >> 6) * group; j0 < n; j0 += kPrepThreads / 64 * group) {
-      const int l = tid & 63;
-      const bool in = l < group && j0 + l < n;
-      const int32_t e = in ? ext_of(j0 + l) : 0;
-      const unsigned long long mk = in ? gmask_of(j0 + l) : 0;
-      const int count = blocks_of(e) * h_kv;
-      if (count <= group)
-        for (int i = 0; i < count; ++i) emit(f, j0 + l, e, mk, i);
-      unsigned long long wide =
-          __builtin_amdgcn_ballot_w64(count > group && !(coop && count > kCoopItems));
-      for (; wide; wide &= wide - 1) {
+    const int l = tid & 63;
+    int64_t j0 = (int64_t)(tid >> 6) * group, first = 0;   // next group; the current one
+    int32_t e = 0;
+    unsigned long long mk = 0, wide = 0;   // wide: samples of the group that the wave enumerates
+    for (int k = 0;;) {
+      int64_t j;
+      int32_t ej;
+      unsigned long long mj;
+      int i, step;
+      if (wide) {
         const int s = __builtin_ctzll(wide);
-        const int32_t es = __shfl(e, s);
-        const unsigned long long ms = __shfl(mk, s);
-        for (int i = l; i < blocks_of(es) * h_kv; i += 64) emit(f, j0 + s, es, ms, i);
+        wide &= wide - 1;
+        j = first + s;
+        ej = __shfl(e, s);
+        mj = __shfl(mk, s);
+        i = l;
+        step = 64;
+      } else if (j0 < n) {
+        first = j0;
+        j0 += kPrepThreads / 64 * group;
+        j = first + l;
+        const bool in = l < group && j < n;
+        e = in ? ext_of(j) : 0;
+        mk = in ? gmask_of(j) : 0;
+        const int count = blocks_of(e) * h_kv;
+        wide = __builtin_amdgcn_ballot_w64(count > group && !(coop && count > kCoopItems));
+        ej = count <= group ? e : 0;
+        mj = mk;
+        i = 0;
+        step = 1;
+      } else if (coop && k < lds.n_long) {
+        j = lds.longs[k++];
+        ej = ext_of(j);
+        mj = gmask_of(j);
+        i = tid;
+        step = kPrepThreads;
+      } else {
+        break;
       }
-    }
-    if (!coop) return;
-    for (int k = 0; k < lds.n_long; ++k) {
-      const int64_t j = lds.longs[k];
-      const int32_t e = ext_of(j);
-      const unsigned long long mk = gmask_of(j);
-      const int count = blocks_of(e) * h_kv;
-      for (int i = tid; i < count; i += kPrepThreads) emit(f, j, e, mk, i);
+      for (const int count = blocks_of(ej) * h_kv; i < count; i += step) emit(f, j, ej, mj, i);
     }
   };
   // Split rows: when the longest item takes a quarter longer than the whole
   // call would if its work were spread evenly (few KV heads and samples: a 4K
   // pack has 70 items for 256 workgroups), the items longer than half of a
   // workgroup's share are cut into parts of C row blocks, summed by
-  // bwd_dkdv_combine_kernel.  C is at least kBwdSplitMinBlocks and doubles
-  // until the parts fit the slots.  Below that line a part's own cost (K / V
+  // bwd_dkdv_combine_kernel.  C is at least kBwdSplitMinBlocks and so large that
+  // the parts fit the slots: items longer than C number at most work / C, their
+  // parts twice that.  Below that line a part's own cost (K / V
   // loads, the fill of the ring, fp32 sums written and read) takes the gain:
   // 46 row blocks against a share of 4.6 (4K tokens, 2 KV heads, d = 64): 119 us
   // whole, 51 split; 430 against 391 (20K tokens, 4 KV heads): 908 and 935.
-  {
+  //
+  // Where the tiles cover every row of the samples up to their extents, an item is
+  // as long as the extent past its first key.  Elsewhere (a context-parallel share,
+  // a single tile, a pool worker's tiles) the extent is only a bound: when the line is
+  // crossed by the extents, the steps of the covered rows are counted, and rule and
+  // cuts go by them, so that no part is without rows.  (By extents, 446 of the 553
+  // parts of a 3K-row share of 48K tokens with 4 / 1 heads were: its backward took
+  // 267 us, now 180; a tile of 2400 rows deep in a 48K sample 245, now 206, uncut.)
+  auto by_extent = [&](const BwdItem &it, int32_t e) {
+    return (e - it.kb * kBwdBK + kRows - 1) / kRows;
+  };
+  // longest item and sum of all (pass 0: by extent, 1: by steps): crosses the line?
+  auto crosses = [&](int pass, auto &&cost) {
     unsigned long long w = 0;
     int32_t m = 0;
-    whole([&](const BwdItem &, int cost, int) {
-      w += (unsigned long long)cost;
-      m = max(m, cost);
+    whole([&](const BwdItem &it, int32_t e, int) {
+      const int c = cost(it, e);
+      w += (unsigned long long)c;
+      m = max(m, c);
     });
     if (m) {
-      atomicAdd(&lds.work, w);
-      atomicMax(&lds.longest, m);
+      atomicAdd(at0(&lds.work[pass]), w);
+      atomicMax(at0(&lds.longest[pass]), m);
     }
-  }
-  __syncthreads();
-  const unsigned long long half = lds.work / (2ull * (unsigned)a.grid);
-  if (4ull * (unsigned)lds.longest * (unsigned)a.grid > 5ull * lds.work &&
-      lds.longest >= 2 * kBwdSplitMinBlocks) {
-    int c = (int)max(half, (unsigned long long)kBwdSplitMinBlocks);
-    for (;; c *= 2) {   // ends: no item is longer than 2^26 blocks
-      if (tid == 0) lds.parts = 0;
-      __syncthreads();
-      whole([&](const BwdItem &, int cost, int) {
-        if (cost > c) atomicAdd(&lds.parts, (unsigned long long)((cost + c - 1) / c));
-      });
-      __syncthreads();
-      const bool fits = lds.parts <= (unsigned long long)kBwdSplitSlots;
-      __syncthreads();
-      if (fits) break;
+    __syncthreads();
+    return 4ull * (unsigned)lds.longest[pass] * (unsigned)a.grid > 5ull * lds.work[pass] &&
+           lds.longest[pass] >= 2 * kBwdSplitMinBlocks;
+  };
+  // Steps (32 covered rows x two heads of one tile), times 32, of each (sample, key
+  // block, KV head): `cov` those of the block's own 128 rows, cov_sum those of all
+  // rows from it on, which attend it; in LDS if the key blocks reached fit there, else
+  // in the workspace, where a sample's places come past those of the samples before it.
+  const bool cov_lds = in_lds && (int64_t)lds.taken * h_kv <= kPlaces;
+  auto lds_place = [&](int j, int kb, int g) { return (lds.at[j] + kb) * h_kv + g; };
+  auto ws_place = [&](int64_t j, int kb, int g) { return (cu[j] / kBwdBK + j + kb) * h_kv + g; };
+  auto steps_of = [&](int j, int kb, int g) {
+    return (unsigned)(cov_lds ? lds.cov_sum[lds_place(j, kb, g)]
+                              : ld_agent(&a.cov_sum[ws_place(j, kb, g)]));
+  };
+  auto sync_cov = [&]() {
+    if (!cov_lds) __threadfence();
+    __syncthreads();
+  };
+  bool split = crosses(0, by_extent), counted = split && lds.covered != lds.reached;
+  if (counted) {
+    if (!cov_lds) {
+      whole([&](const BwdItem &it, int32_t, int) { a.cov[ws_place(it.sample, it.kb, it.g)] = 0; });
+      sync_cov();
     }
-    if (tid == 0) lds.chunk = c;
-  }
-  __syncthreads();
-  const int chunk = lds.chunk;   // 0: no item is split
-  auto each = [&](auto &&f, bool scatter) {
-    whole([&](const BwdItem &it, int cost, int x) {
-      if (chunk == 0 || cost <= chunk) {
-        f(it, (int64_t)cost, x);
-        return;
+    const int64_t windows = (lds.tile_rows + kBwdBK - 1) / kBwdBK;
+    for (int64_t v = tid; v < T * windows; v += kPrepThreads) {
+      const bool small = T * windows < INT32_MAX;   // a 32-bit division, not a 64-bit one
+      const int64_t t = small ? (int64_t)((uint32_t)v / (uint32_t)windows) : v / windows;
+      const libra_tile_t tl = a.tiles[t];
+      if (!tile_ok(tl, n_q, n_kv, h_q)) continue;
+      const int64_t wa = tl.q_begin + kBwdBK * (v - t * windows);
+      const int64_t wb = wa + kBwdBK < tl.q_end ? wa + kBwdBK : tl.q_end;
+      if (wa >= wb) continue;
+      for (int64_t j = upper_bound64(cu, n, wa) - 1; j < n && cu[j] < wb; ++j) {
+        const int la = (int)((wa > cu[j] ? wa : cu[j]) - cu[j]);
+        const int lb = (int)((wb < cu[j + 1] ? wb : cu[j + 1]) - cu[j]);
+        for (int kb = la / kBwdBK; kb * kBwdBK < lb && la < lb; ++kb) {
+          const int rows = min(lb, kb * kBwdBK + kBwdBK) - max(la, kb * kBwdBK);
+          for (int g = tl.head_begin / G; g * G < tl.head_end; ++g) {
+            const int nh = min(tl.head_end, (g + 1) * G) - max(tl.head_begin, g * G);
+            const int x = rows * ((nh + 1) / 2);
+            if (cov_lds) atomicAdd(&lds.hist[lds_place((int)j, kb, g)], x);
+            else atomicAdd(&a.cov[ws_place(j, kb, g)], x);
+          }
+        }
       }
-      const int np = (cost + chunk - 1) / chunk, per = (cost + np - 1) / np;
+    }
+    sync_cov();
+    // The sums block by block (the line is crossed by samples of at most some 400
+    // blocks), kept below 2^31 whatever overlapping tiles count; and the most that
+    // one block holds
+    int most_block = 0;
+    split = crosses(1, [&](const BwdItem &it, int32_t e) {
+      const int count = blocks_of(e) - it.kb;
+      const unsigned most = 0x7fffffffu / (unsigned)blocks_of(e);
+      unsigned s = 0;
+      auto add = [&](int x) { s += min((unsigned)x, most); };
+      if (cov_lds) {
+        const int at = lds_place(it.sample, it.kb, it.g);
+#pragma unroll 16
+        for (int i = 0; i < count; ++i) add(lds.hist[at + i * h_kv]);
+        most_block = max(most_block, lds.hist[at]);
+        lds.cov_sum[at] = (int32_t)s;
+      } else {
+        const int64_t at = ws_place(it.sample, it.kb, it.g);
+#pragma unroll 8
+        for (int i = 0; i < count; ++i) add(ld_agent(&a.cov[at + (int64_t)i * h_kv]));
+        most_block = max(most_block, ld_agent(&a.cov[at]));
+        a.cov_sum[at] = (int32_t)s;
+      }
+      return (int)((s + kRows - 1) / kRows);
+    });
+    if (most_block) atomicMax(at0(&lds.block), most_block);
+    counted = split;   // else every item stays whole, ordered by extent
+    sync_cov();
+  }
+  // C; 0: no item is split.  By extent, it is half of a workgroup's share, and the
+  // parts of an item are equal row ranges.  By steps, items are cut from the last
+  // row back, so that those of a sample share their cuts: C each, and the first
+  // one takes the rest.  Such parts fill the rounds of a launch better when they are
+  // a whole share: counted on the host, 51 calls take 0.82 of the time of cuts by
+  // extent, 0.84 with half shares.  C is no less than one key block's steps, so that
+  // a part has rows.
+  const unsigned long long work = lds.work[counted];
+  const unsigned block = (unsigned)lds.block;
+  const int least = max(kBwdSplitMinBlocks, counted ? (int)((block + kRows - 1) / kRows) : 0);
+  const int chunk =
+      split ? (int)max(work / ((counted ? 1ull : 2ull) * (unsigned)a.grid),
+                       max((2 * work + kBwdSplitSlots - 1) / kBwdSplitSlots,
+                           (unsigned long long)least))
+            : 0;
+  const unsigned part = (unsigned)min((unsigned long long)chunk * kRows, 1ull << 31);
+  // Cut m of a (sample, KV head), in blocks of 32 rows: the first key block from which
+  // on there are no more than m C steps, or inside the one before it if that is as
+  // full as any, so that m C remain.  It takes the place of key block m, where the
+  // counts are not needed any more.  Written in the counting pass of build_queues, by
+  // the items before and after which it lies, for every m that an item can ask for.
+  auto write_cuts = [&](const BwdItem &it, int nb, unsigned s0) {
+    const int next = it.kb + 1;
+    const unsigned s1 = next < nb ? steps_of(it.sample, next, it.g) : 0;
+    for (unsigned m = max(1u, (s1 + part - 1) / part); m < (unsigned)nb && m * part < s0; ++m) {
+      const unsigned more = s0 - s1 == block ? (m * part - s1) * 4ull / block : 0;   // < 4
+      const int c = kBwdBK / kRows * next - (int)more;
+      if (cov_lds) lds.cuts[lds_place(it.sample, (int)m, it.g)] = (uint16_t)c;
+      else a.cov[ws_place(it.sample, (int)m, it.g)] = c;
+    }
+    if (!cov_lds) __threadfence();
+  };
+  auto cut = [&](int j, int g, int m) {
+    return kRows * (cov_lds ? lds.cuts[lds_place(j, m, g)] : ld_agent(&a.cov[ws_place(j, m, g)]));
+  };
+  auto each = [&](auto &&f, bool scatter) {
+    whole([&](const BwdItem &it, int32_t e, int x) {
+      int cost = by_extent(it, e), np = 1, per = chunk;
+      if (counted) {
+        const unsigned s = steps_of(it.sample, it.kb, it.g);
+        cost = (int)((s + kRows - 1) / kRows);
+        np = max(1, min((int)((s + part - 1) / part), blocks_of(e) - it.kb));
+        if (!scatter) write_cuts(it, blocks_of(e), s);
+      } else if (chunk && cost > chunk) {
+        np = (cost + chunk - 1) / chunk;
+        per = (cost + np - 1) / np;
+      }
       int32_t base = 0;
-      if (scatter) {
-        base = atomicAdd(&lds.nslot, np);
+      if (scatter && np > 1) {
+        base = atomicAdd(at0(&lds.nslot), np);
         a.splits[atomicAdd(&lds.nsplit, 1)] = BwdSplit{it, base, np, 0, 0};
       }
+      // the odd part: the first one by steps, the last one by extent
+      const int odd_part = counted ? 0 : np - 1, odd_cost = max(cost - per * (np - 1), 1);
+      BwdItem ip = it;
       for (int p = 0; p < np; ++p) {
-        BwdItem ip = it;
-        ip.slot = base + p;
-        ip.r0 = it.kb * kBwdBK + kRows * per * p;
-        if (p + 1 < np) ip.r1 = ip.r0 + kRows * per;
-        f(ip, (int64_t)(p + 1 < np ? per : max(cost - per * p, 1)), x);
+        if (scatter && np > 1) {
+          ip.slot = base + p;
+          ip.r0 = p ? ip.r1 : it.kb * kBwdBK;
+          ip.r1 = p + 1 == np ? INT32_MAX
+                  : counted   ? cut(it.sample, it.g, np - 1 - p)
+                              : ip.r0 + kRows * per;
+        }
+        f(ip, (int64_t)(p == odd_part ? odd_cost : per), x);
       }
     });
   };
@@ -1137,7 +1299,8 @@ static size_t align256b(size_t x) { return (x + 255) / 256 * 256; }
 BwdLayout bwd_layout(int64_t T, int64_t n, int64_t n_q, int64_t n_kv, int h_q, int h_kv, int d) {
   BwdLayout L;
   // a split item's parts take its place: kBwdSplitSlots of them at most
-  L.max_items = (n_kv / kBwdBK + n + 1) * (int64_t)h_kv + kBwdSplitSlots;
+  L.max_blocks = (n_kv / kBwdBK + n + 1) * (int64_t)h_kv;
+  L.max_items = L.max_blocks + kBwdSplitSlots;
   L.max_qitems = fwd_max_items(T, n, n_q, h_q, h_kv);
   L.nq_pad = (n_q + kRows - 1) / kRows * kRows;
   L.hdr = 0;
@@ -1153,8 +1316,9 @@ BwdLayout bwd_layout(int64_t T, int64_t n, int64_t n_q, int64_t n_kv, int h_q, i
   L.splits = align256b(L.stats + (size_t)h_q * L.nq_pad * 2 * sizeof(float));
   L.max_parts = kFwdSplitSlots;
   L.bsplits = align256b(L.splits + (size_t)(L.max_parts / 2) * sizeof(FwdSplit));
+  L.cov = align256b(L.bsplits + (size_t)(kBwdSplitSlots / 2) * sizeof(BwdSplit));
   // the partial slots serve the dQ kernel, then the dK / dV kernel
-  L.parts = align256b(L.bsplits + (size_t)(kBwdSplitSlots / 2) * sizeof(BwdSplit));
+  L.parts = align256b(L.cov + (size_t)L.max_blocks * 2 * sizeof(int32_t));
   L.total = align256b(L.parts + (size_t)L.max_parts * fwd_part_floats(d) * sizeof(float));
   return L;
 }
@@ -1175,6 +1339,7 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
   f16 *k16 = reinterpret_cast<f16 *>(ws + L.k16);
   f16 *v16 = reinterpret_cast<f16 *>(ws + L.v16);
   float *stats = reinterpret_cast<float *>(ws + L.stats);
+  int32_t *cov = reinterpret_cast<int32_t *>(ws + L.cov);
   static bool attr_set = false;
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bwd_dkdv_kernel<D>),
@@ -1206,7 +1371,8 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
     const int max_parts = may_split(n_kv) ? L.max_parts : 0;
     hipLaunchKernelGGL(prep_bwd_kernel, dim3(2), dim3(kPrepThreads), 0, st,
                        BwdPrep{cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, ext, gmask, items,
-                               L.max_items, cus, reinterpret_cast<BwdSplit *>(ws + L.bsplits)},
+                               L.max_items, cus, reinterpret_cast<BwdSplit *>(ws + L.bsplits), cov,
+                               cov + L.max_blocks},
                        FwdPrep{cu, n, tiles, T, h_q, h_kv, n_q, n_kv, hdr, qitems, L.max_qitems, 0,
                                cus, cus, max_parts, 1, splits});
     // K and V rows: at least eight for a wave (every workgroup that finds a new

@@ -650,9 +650,9 @@ struct FwdLayout {
 };
 struct BwdLayout {
   size_t hdr = 0, ext = 0, gmask = 0, items = 0, qitems = 0, rec = 0, k16 = 0,
-         v16 = 0, stats = 0, splits = 0, bsplits = 0, parts = 0, total = 0;
+         v16 = 0, stats = 0, splits = 0, bsplits = 0, cov = 0, parts = 0, total = 0;
   int32_t max_parts = 0;   // split-K partial slots of the dQ kernel
-  int64_t max_items = 0, max_qitems = 0, nq_pad = 0;
+  int64_t max_blocks = 0, max_items = 0, max_qitems = 0, nq_pad = 0;
 };
 
 // `split`: room for split-K partial results (libra_attn_fwd); without it the
