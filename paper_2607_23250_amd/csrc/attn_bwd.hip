@@ -427,7 +427,8 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
       }
     });
   };
-  build_queues<BwdItem>(each, lds.hist, lds.part, hdr, kBwdQ, a.items, a.max_items, a.grid);
+  build_queues<BwdItem>(each, lds.hist, lds.part, hdr, kBwdQ, kBadTiles, a.items, a.max_items,
+                        a.grid);
   __syncthreads();
   if (tid == 0) hdr[kBwdSplits] = lds.nsplit;
 }
@@ -697,6 +698,7 @@ struct BwdPass {
 template <int D>
 __global__ __launch_bounds__(256) void bwd_max_kernel(BwdPass a) {
   unsigned b = blockIdx.x;
+  if (b == 0 && threadIdx.x == 0 && a.hdr[kDqFull]) atomicAdd(&a.hdr[kBadTiles], 1);
   if (b < a.kv_blocks) {
     kv_pass<D, false>(b, a.kv_blocks, a.k, a.v, a.cu, a.n, a.ext, a.h_kv, a.n_kv, a.hdr, a.k16,
                       a.v16);

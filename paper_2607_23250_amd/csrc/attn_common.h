@@ -46,6 +46,7 @@ enum HdrSlot {
   kBadTiles = 4,   // tiles skipped because they were out of range (+1 on item overflow)
   kOddHeads = 5,   // backward: some tile covers an odd number of a KV group's heads
   kBwdSplits = 6,  // backward: split dK / dV items (BwdSplit records)
+  kDqFull = 7,     // backward: the dQ item list overflowed
   kFwdQ = 8,       // forward / dQ work items
   kBwdQ = 32,      // dK/dV work items
   kMaxAbs = 56,    // backward: max |x| (fp32 bits) of Q, dO, K, V in slots 56..59
@@ -93,10 +94,11 @@ __device__ __forceinline__ int cost_bucket(int64_t c) {
 // items with the same costs and queues in both passes (scatter = false:
 // counting, then true: placing).  `grid`: workgroups of the kernel that runs
 // the items; the queue heads start past the items that they take without
-// asking (take_item).
+// asking (take_item).  `full`: header slot that counts an overflow of the list,
+// zeroed by this workgroup before.
 template <typename Item, typename Each>
 __device__ void build_queues(Each &&each, int32_t *hist, int32_t *part, int32_t *hdr, int base,
-                             Item *out, int64_t max_items, int grid) {
+                             int full, Item *out, int64_t max_items, int grid) {
   const int tid = threadIdx.x;
   for (int i = tid; i < kXcds * kQBuckets; i += kPrepThreads) hist[i] = 0;
   __syncthreads();
@@ -130,7 +132,7 @@ __device__ void build_queues(Each &&each, int32_t *hist, int32_t *part, int32_t 
     hdr[head_slot(base, x)] = (grid - x + kXcds - 1) / kXcds;
     hdr[base + kXcds + x] = (end < lim ? end : lim) - (start < lim ? start : lim);
     hdr[base + 2 * kXcds + x] = start;
-    if (x == kXcds - 1 && end > lim) atomicAdd(&hdr[kBadTiles], 1);
+    if (x == kXcds - 1 && end > lim) atomicAdd(&hdr[full], 1);
   }
   __syncthreads();
   for (int i = 0; i < per; ++i) {

@@ -45,7 +45,9 @@ __device__ void for_each_fwd_item_in(const libra_tile_t &t, int64_t wa, int64_t 
 // One workgroup: every tile's items, longest-first, one queue per XCD keyed
 // by (KV head, head chunk) so that an XCD streams few K/V sequences.  Tiles
 // outside the buffers are skipped, and counted in hdr[kBadTiles] when
-// `count_bad` is set (the backward counts them in its own preparation pass).
+// `count_bad` is set.  The backward counts them in the dK / dV part of its
+// preparation, which runs beside this one and zeroes that slot, so an overflow of
+// this list goes to a slot of its own there (hdr[kDqFull]).
 //
 // Split K: when there are fewer than two items per workgroup of `split_grid`
 // (few rows and heads against long samples), and with
@@ -97,7 +99,7 @@ __device__ __forceinline__ void prep_fwd(const FwdPrep &a, FwdPrepLds &lds) {
   const int keys = h_kv * chunks;
   const int R = keys >= kXcds ? 1 : kXcds / keys;    // queues per key
   if (tid == 0) {
-    if (a.count_bad) hdr[kBadTiles] = 0;
+    hdr[a.count_bad ? kBadTiles : kDqFull] = 0;
     hdr[kFwdSplits] = 0;
     hdr[kFwdSplits + 1] = 0;
     s_wmax = 0;
@@ -197,7 +199,8 @@ __device__ __forceinline__ void prep_fwd(const FwdPrep &a, FwdPrepLds &lds) {
       }
     });
   };
-  build_queues<FwdItem>(each, lds.hist, lds.part, hdr, kFwdQ, a.items, a.max_items, a.grid);
+  build_queues<FwdItem>(each, lds.hist, lds.part, hdr, kFwdQ,
+                        a.count_bad ? kBadTiles : kDqFull, a.items, a.max_items, a.grid);
   __syncthreads();
   if (tid == 0) {
     hdr[kFwdSplits] = s_nsplit;

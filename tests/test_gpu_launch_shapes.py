@@ -105,3 +105,23 @@ def test_few_long_kv_items_split_rows(h_q, h_kv, d, n):
     _, dK, dV = oa.attention_bwd(q.cpu(), k.cpu(), v.cpu(), do.cpu(), lengths, np.arange(rows))
     check("dK", to_np(a[1]), dK, bf16_out=True)
     check("dV", to_np(a[2]), dV, bf16_out=True)
+
+
+def test_overflow_of_the_dq_items_is_reported():
+    """200 copies of a tile make more dQ items than the workspace holds (it is
+    sized for tiles that do not overlap): the ones that fit run, and the count of
+    skipped tiles says so, once for the forward list, once for the dQ list."""
+    n, T = 4096, 200
+    tiles = _tiles([(0, n, 0, 1)] * T)
+    q, k, v, do = (t.to(DEV) for t in wl.tensors(5, n, n, 1, 1, 64))
+    cu = torch.tensor([0, n], dtype=torch.int64, device=DEV)
+    td = pl.tiles_to_device(tiles, DEV)
+    assert T * (n // 128) > n // 64 + (T + 1) * 2 + 1 + 3072
+    ws = pl.alloc_workspace(max(pl.libra_attn_workspace_size(T, 1, n, n, 1, 1, 64, b)
+                                for b in (False, True)), DEV)
+    say(f"[overflow] {T} copies of a tile of {n} rows")
+    for _ in range(3):
+        o, lse = pl.libra_attn_fwd(q, k, v, cu, td, workspace=ws)
+        assert pl.libra_attn_skipped_tiles(ws) == 1
+        pl.libra_attn_bwd(q, k, v, o, lse, do, cu, td, workspace=ws)
+        assert pl.libra_attn_skipped_tiles(ws) == 1
