@@ -609,7 +609,7 @@ __device__ __forceinline__ void pre_pass(unsigned block, const bf16 *__restrict_
                                          const float *__restrict__ lse,
                                          const libra_tile_t *__restrict__ tiles, int h_q,
                                          int64_t n_q, int64_t n_kv, int64_t nq_pad, float scale,
-                                         const int32_t *__restrict__ hdr,
+                                         int64_t pool, const int32_t *__restrict__ hdr,
                                          f16 *__restrict__ rec, float *__restrict__ stats) {
   const int tid = threadIdx.x;
   const libra_tile_t tl = tiles[block / kTileSplit];
@@ -659,6 +659,9 @@ __device__ __forceinline__ void pre_pass(unsigned block, const bf16 *__restrict_
         static_for<8>([&](auto i) { sv[int(i)] = f16(0.f); });
         *reinterpret_cast<f16x8 *>(ag + kAugEl / 4) = sv;
         *reinterpret_cast<f16x8 *>(ag + 3 * (kAugEl / 4)) = sv;
+        // past the last sample no dQ item writes the second operand
+        if (tl.q_begin + (row - ra) >= pool)
+          *reinterpret_cast<f16x8 *>(ag + 2 * (kAugEl / 4)) = sv;
       }
     }
   }
@@ -718,7 +721,7 @@ __global__ __launch_bounds__(256) void bwd_copy_kernel(BwdPass a) {
                      a.v16);
   else
     pre_pass<D>(b - a.kv_blocks, a.q, a.o, a.dout, a.lse, a.tiles, a.h_q, a.n_q, a.n_kv, a.nq_pad,
-                a.scale, a.hdr, a.rec, a.stats);
+                a.scale, a.cu[a.n], a.hdr, a.rec, a.stats);
 }
 
 // ---------------------------------------------------------------------------

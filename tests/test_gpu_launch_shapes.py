@@ -125,3 +125,31 @@ def test_overflow_of_the_dq_items_is_reported():
         assert pl.libra_attn_skipped_tiles(ws) == 1
         pl.libra_attn_bwd(q, k, v, o, lse, do, cu, td, workspace=ws)
         assert pl.libra_attn_skipped_tiles(ws) == 1
+
+
+@pytest.mark.parametrize("d", (64, 128))
+def test_tiles_past_the_last_sample(d):
+    """K and V buffers longer than the samples, and tiles that reach past them: the
+    rows there attend nothing and leave the others' gradients alone, whatever the
+    workspace held before."""
+    n, rows, h_q, h_kv = 200, 300, 4, 2
+    tiles = _tiles([(0, 90, 0, 4), (90, rows, 0, 4)])
+    q, k, v, do = wl.tensors(5, rows, rows, h_q, h_kv, d)
+    qd, kd, vd, dod = (t.to(DEV) for t in (q, k, v, do))
+    cu = torch.tensor([0, 70, n], dtype=torch.int64, device=DEV)
+    td = pl.tiles_to_device(tiles, DEV)
+    o = torch.zeros_like(qd)
+    lse = torch.zeros((h_q, rows), dtype=torch.float32, device=DEV)
+    dq = torch.zeros_like(qd)
+    ws = pl.alloc_workspace(max(pl.libra_attn_workspace_size(2, 2, rows, rows, h_q, h_kv, d, b)
+                                for b in (False, True)), DEV)
+    say(f"[past the samples] d={d}")
+    pl.libra_attn_fwd(qd, kd, vd, cu, td, o=o, lse=lse, workspace=ws)
+    ws.fill_(0xFF)
+    _, dk, dv = pl.libra_attn_bwd(qd, kd, vd, o, lse, dod, cu, td, dq=dq, workspace=ws)
+    torch.cuda.synchronize()
+    dQ, dK, dV = oa.attention_bwd(q[:n], k[:n], v[:n], do[:n], [70, n - 70], np.arange(n))
+    check("dQ", to_np(dq)[:n], dQ, bf16_out=True)
+    check("dK", to_np(dk)[:n], dK, bf16_out=True)
+    check("dV", to_np(dv)[:n], dV, bf16_out=True)
+    assert not to_np(dq)[n:].any() and not to_np(dk)[n:].any() and not to_np(dv)[n:].any()
