@@ -1403,9 +1403,10 @@ static int launch_bwd_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 
     hipLaunchKernelGGL(attn_bwd_dkdv_kernel<D>, dim3(cus), dim3(kThreads), KvShape<D>::SMEM, st,
                        k16, v16, rec, cu, tiles, T, items, hdr, h_q, h_kv, n_q, n_kv, scale,
                        scale * kLog2e, dk, dv, accumulate ? 1 : 0, parts);
-    hipLaunchKernelGGL(bwd_dkdv_combine_kernel<D>, dim3(cus * 4), dim3(256), 0, st,
-                       reinterpret_cast<const BwdSplit *>(ws + L.bsplits), hdr, parts, cu, h_kv,
-                       scale, dk, dv, accumulate ? 1 : 0);
+    if (may_split_rows(n_kv))
+      hipLaunchKernelGGL(bwd_dkdv_combine_kernel<D>, dim3(cus * 4), dim3(256), 0, st,
+                         reinterpret_cast<const BwdSplit *>(ws + L.bsplits), hdr, parts, cu, h_kv,
+                         scale, dk, dv, accumulate ? 1 : 0);
     if (tm_kv) hipEventRecord(tm_kv->end, st);
   }
   const hipError_t e = hipGetLastError();

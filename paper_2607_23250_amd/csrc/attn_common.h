@@ -274,6 +274,10 @@ struct BwdSplit {
 };
 constexpr int kBwdSplitMinBlocks = 8;              // a part walks at least 8 row blocks
 constexpr int kBwdSplitSlots = kFwdSplitSlots / 2; // a part takes two slots
+// Can a call split an item's rows?  Only one of two parts or more.
+__host__ __device__ constexpr bool may_split_rows(int64_t n_kv) {
+  return n_kv > kRows * (2 * (int64_t)kBwdSplitMinBlocks - 1);
+}
 
 // Swap bits 2 and 3 of a row index: reading MFMA operand rows in this order
 // makes the 16 accumulator registers of a lane hold 8 + 8 contiguous rows.

@@ -95,6 +95,9 @@ CALLS = {
     "one head to a tile": ([6000, 2192], _share([6000, 2192], 4), 512, 4, (4, 2), 64, True),
     # more samples than the counts in LDS are kept for
     "many samples": ([4] * 1100 + [6000], [(0, 400), (9600, 10400)], 400, 1, (2, 1), 64, True),
+    # one row block below two parts (no merge is launched), and two
+    "480 rows": ([480], None, 480, 1, (2, 1), 64, False),
+    "481 rows": ([481, 1], None, 482, 1, (2, 1), 64, True),
     "all rows": ([4096, 512], None, 300, 2, (8, 2), 64, True),
 }
 
