@@ -52,12 +52,12 @@ def _check(lengths, tiles, h_q, h_kv, d, seed=5):
     assert not to_np(dk)[:, other].any() and not to_np(dv)[:, other].any()
 
 
-@pytest.mark.parametrize("n_items", (1, 32, 33, 64, 65, 700, 1025, 2048))
+@pytest.mark.parametrize("n_items", (1, 32, 33, 64, 65, 96, 97, 700, 1025, 2048))
 def test_one_queue_holds_every_item(n_items):
     """One of eight heads (no grouping): all items lie in one queue.  With more
-    of them than its own workgroups (64 of the forward, 32 of the backward) the
-    others have to come from the seven empty queues; with fewer, every
-    workgroup has to find its way out.  From 1025 samples on their extents, and
+    of them than its own workgroups (96 of the forward at d = 64, 32 of the
+    backward) the others have to come from the seven empty queues; with fewer,
+    every workgroup has to find its way out.  From 1025 samples on their extents, and
     from 2048 on their offsets, stay in memory during the preparation."""
     lengths = [int(x) for x in np.random.default_rng(n_items).integers(1, 60, n_items)]
     n = sum(lengths)
@@ -82,13 +82,14 @@ def test_head_ranges_and_shared_row_blocks(cuts, d):
     _check(lengths, _tiles(spans), 8, 2, d)
 
 
-@pytest.mark.parametrize("h_q,h_kv,d,n", [(2, 1, 64, 511), (4, 2, 128, 513), (3, 1, 64, 1200),
-                                          (2, 2, 128, 2049), (8, 2, 64, 4096)])
+@pytest.mark.parametrize("h_q,h_kv,d,n", [(2, 1, 64, 480), (2, 1, 64, 481), (2, 1, 64, 511),
+                                          (4, 2, 128, 513), (3, 1, 64, 1200), (2, 2, 128, 2049),
+                                          (8, 2, 64, 4096)])
 def test_few_long_kv_items_split_rows(h_q, h_kv, d, n):
     """One or two samples and few KV heads: the dK / dV items are longer than
     the share of a workgroup and are cut into row ranges whose partial sums are
-    merged; 511 rows are just below two parts.  Tiles that end inside the
-    parts; both output modes; the same bits from one call to the next."""
+    merged, from 481 rows on (16 row blocks, two parts).  Tiles that end inside
+    the parts; both output modes; the same bits from one call to the next."""
     lengths = [n, 77]
     rows = n + 77
     spans = [(a, min(a + 301, rows), 0, h_q) for a in range(0, rows, 301)]
@@ -99,8 +100,11 @@ def test_few_long_kv_items_split_rows(h_q, h_kv, d, n):
     cu = torch.tensor([0, n, rows], dtype=torch.int64, device=DEV)
     td = pl.tiles_to_device(tiles, DEV)
     o, lse = pl.libra_attn_fwd(q, k, v, cu, td)
-    a, b = (pl.libra_attn_bwd(q, k, v, o, lse, do, cu, td) for _ in range(2))
+    ws = pl.alloc_workspace(pl.libra_attn_workspace_size(len(tiles), 2, rows, rows, h_q, h_kv, d,
+                                                         True), DEV)
+    a, b = (pl.libra_attn_bwd(q, k, v, o, lse, do, cu, td, workspace=ws) for _ in range(2))
     torch.cuda.synchronize()
+    assert (int(ws[24:28].view(torch.int32)) > 0) == (n > 480)   # header slot kBwdSplits
     assert all(torch.equal(x, y) for x, y in zip(a, b))
     _, dK, dV = oa.attention_bwd(q.cpu(), k.cpu(), v.cpu(), do.cpu(), lengths, np.arange(rows))
     check("dK", to_np(a[1]), dK, bf16_out=True)
