@@ -45,9 +45,9 @@ struct DqShape {
 // The kernel runs at the power limit of the card (6 d flops per pair at 1.25
 // PFLOP/s, against 1.56 of a large matrix product), so what it saves in
 // instructions shows little: operand addresses from two registers instead of
-// eight (swu, which also ended the spills) and reads four products ahead
-// instead of three took 4.03 ms to 4.00 on a 32K pack, 64.8 to 64.6 on the 256K
-// share.  One barrier per block; a 4-stage K / V ring (block i read by the S^T and
+// eight (swu, which also ended the spills) and row reads four products ahead
+// instead of three (the transpose reads stay three ahead) took 4.03 ms to 4.00 on a
+// 32K pack, 64.8 to 64.6 on the 256K share.  One barrier per block; a 4-stage K / V ring (block i read by the S^T and
 // dP^T products, block i - 1 by the dQ^T products, blocks i + 1 and i + 2
 // land).
 template <int D>

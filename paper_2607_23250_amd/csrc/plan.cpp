@@ -1,7 +1,7 @@
 // Host planner: SH-Tiles (Eq. 5), tile cost (Eq. 6), KV groups (Eq. 7),
 // communication increment (Eq. 8) and the communication-aware placement of
 // Algorithm 2 (Sec. 4.3 of the Libra paper).  Pure integer arithmetic; the
-// capacity test of Algorithm 2 is evaluated exactly with 128-bit products.
+// capacity test of Algorithm 2 compares with the floor of an exact quotient.
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
