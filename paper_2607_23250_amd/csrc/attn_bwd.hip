@@ -495,24 +495,31 @@ constexpr int kTileSplit = 64;
 // covered (row, head) pairs; and, in the records, zeros for the rows of the
 // tile's first and last 32-row blocks that lie outside the tile (the dK / dV
 // kernel stages whole records; rows no tile covers must hold finite values,
-// since they meet P = dS = 0 in its products).
+// since they meet P = dS = 0 in its products).  So must the -D operand of a tile's
+// rows past the last sample (position `pool` on), which no dQ item writes.
 template <int D>
 __device__ __forceinline__ void absmax_q(unsigned block, const bf16 *__restrict__ q,
                                          const bf16 *__restrict__ dout,
                                          const libra_tile_t *__restrict__ tiles, int h_q,
-                                         int64_t n_q, int64_t n_kv, int32_t *__restrict__ hdr,
-                                         f16 *__restrict__ rec) {
+                                         int64_t n_q, int64_t n_kv, int64_t pool,
+                                         int32_t *__restrict__ hdr, f16 *__restrict__ rec) {
   const int tid = threadIdx.x;
   const libra_tile_t tl = tiles[block / kTileSplit];
   if (!tile_ok(tl, n_q, n_kv, h_q)) return;
   const int64_t ra = tl.q_row, rb = tl.q_row + (tl.q_end - tl.q_begin);
   const int r = tid >> 3, part = tid & 7;   // 8 threads per row, 32 rows per pass
+  const int64_t past = tl.q_row + (pool - tl.q_begin);   // first row past the last sample
   float mq = 0.f, mo = 0.f;
   for (int64_t m = ra / kRows + block % kTileSplit; m * kRows < rb; m += kTileSplit) {
     const int64_t row = m * kRows + r;
     const bool ok = row >= ra && row < rb;
     for (int h = tl.head_begin; h < tl.head_end; ++h) {
+      f16 *rp = rec + ((size_t)m * h_q + h) * rec_els(D);
+      f16x8 z;
+      static_for<8>([&](auto i) { z[int(i)] = f16(0.f); });
+      f16 *ag = rp + 2 * kRows * D + 8 * perm32(r);   // the row's lanes of both operands
       if (ok) {
+        if (row >= past && part == 0) *reinterpret_cast<f16x8 *>(ag + 2 * (kAugEl / 4)) = z;
         const size_t off = ((size_t)row * h_q + h) * D + part * (D / 8);
         static_for<D / 64>([&](auto c) {
           mq = fmaxf(mq, absmax8(*reinterpret_cast<const bf16x8 *>(q + off + 8 * c)));
@@ -520,17 +527,12 @@ __device__ __forceinline__ void absmax_q(unsigned block, const bf16 *__restrict_
         });
         continue;
       }
-      f16 *rp = rec + ((size_t)m * h_q + h) * rec_els(D);
-      f16x8 z;
-      static_for<8>([&](auto i) { z[int(i)] = f16(0.f); });
       static_for<D / 64>([&](auto c) {
         const int at = rec_at(r, part * (D / 64) + c);
         *reinterpret_cast<f16x8 *>(rp + at) = z;
         *reinterpret_cast<f16x8 *>(rp + kRows * D + at) = z;
       });
-      // the row's lanes of both augmented operands
-      if (part < 4)
-        *reinterpret_cast<f16x8 *>(rp + 2 * kRows * D + part * (kAugEl / 4) + 8 * perm32(r)) = z;
+      if (part < 4) *reinterpret_cast<f16x8 *>(ag + part * (kAugEl / 4)) = z;
     }
   }
   block_max2_to(mq, mo, &hdr[kMaxAbs + 0], &hdr[kMaxAbs + 1]);
@@ -609,7 +611,7 @@ __device__ __forceinline__ void pre_pass(unsigned block, const bf16 *__restrict_
                                          const float *__restrict__ lse,
                                          const libra_tile_t *__restrict__ tiles, int h_q,
                                          int64_t n_q, int64_t n_kv, int64_t nq_pad, float scale,
-                                         int64_t pool, const int32_t *__restrict__ hdr,
+                                         const int32_t *__restrict__ hdr,
                                          f16 *__restrict__ rec, float *__restrict__ stats) {
   const int tid = threadIdx.x;
   const libra_tile_t tl = tiles[block / kTileSplit];
@@ -659,9 +661,6 @@ __device__ __forceinline__ void pre_pass(unsigned block, const bf16 *__restrict_
         static_for<8>([&](auto i) { sv[int(i)] = f16(0.f); });
         *reinterpret_cast<f16x8 *>(ag + kAugEl / 4) = sv;
         *reinterpret_cast<f16x8 *>(ag + 3 * (kAugEl / 4)) = sv;
-        // past the last sample no dQ item writes the second operand
-        if (tl.q_begin + (row - ra) >= pool)
-          *reinterpret_cast<f16x8 *>(ag + 2 * (kAugEl / 4)) = sv;
       }
     }
   }
@@ -706,7 +705,7 @@ __global__ __launch_bounds__(256) void bwd_max_kernel(BwdPass a) {
     kv_pass<D, false>(b, a.kv_blocks, a.k, a.v, a.cu, a.n, a.ext, a.h_kv, a.n_kv, a.hdr, a.k16,
                       a.v16);
   } else if ((b -= a.kv_blocks) < a.tile_blocks) {
-    absmax_q<D>(b, a.q, a.dout, a.tiles, a.h_q, a.n_q, a.n_kv, a.hdr, a.rec);
+    absmax_q<D>(b, a.q, a.dout, a.tiles, a.h_q, a.n_q, a.n_kv, a.cu[a.n], a.hdr, a.rec);
   } else {
     b -= a.tile_blocks;
     const unsigned half = a.zero_blocks / 2;
@@ -721,7 +720,7 @@ __global__ __launch_bounds__(256) void bwd_copy_kernel(BwdPass a) {
                      a.v16);
   else
     pre_pass<D>(b - a.kv_blocks, a.q, a.o, a.dout, a.lse, a.tiles, a.h_q, a.n_q, a.n_kv, a.nq_pad,
-                a.scale, a.cu[a.n], a.hdr, a.rec, a.stats);
+                a.scale, a.hdr, a.rec, a.stats);
 }
 
 // ---------------------------------------------------------------------------
