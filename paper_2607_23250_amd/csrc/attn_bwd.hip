@@ -363,15 +363,17 @@ __device__ __forceinline__ void prep_bwd(const BwdPrep &a, BwdPrepLds &lds) {
   // C; 0: no item is split.  By extent, it is half of a workgroup's share, and the
   // parts of an item are equal row ranges.  By steps, items are cut from the last
   // row back, so that those of a sample share their cuts: C each, and the first
-  // one takes the rest.  Such parts fill the rounds of a launch better when they are
-  // a whole share: counted on the host, 51 calls take 0.82 of the time of cuts by
-  // extent, 0.84 with half shares.  C is no less than one key block's steps, so that
-  // a part has rows.
+  // one takes the rest.  Such parts fill the workgroups better when they are a
+  // little more than a whole share, so that there are no more of them than
+  // workgroups: counted on the host, 82 calls take 0.78 of the time of cuts by extent,
+  // 0.82 with a share exactly, 0.82 with 1.25 and 0.84 with half a share.  C is no less
+  // than one key block's steps, so that a part has rows.
   const unsigned long long work = lds.work[counted];
   const unsigned block = (unsigned)lds.block;
   const int least = max(kBwdSplitMinBlocks, counted ? (int)((block + kRows - 1) / kRows) : 0);
   const int chunk =
-      split ? (int)max(work / ((counted ? 1ull : 2ull) * (unsigned)a.grid),
+      split ? (int)max(counted ? (work + work / 16) / (unsigned)a.grid
+                               : work / (2ull * (unsigned)a.grid),
                        max((2 * work + kBwdSplitSlots - 1) / kBwdSplitSlots,
                            (unsigned long long)least))
             : 0;

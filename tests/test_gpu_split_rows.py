@@ -125,7 +125,7 @@ def test_parts_hold_covered_rows(name):
     longest, work = check_items(items, splits, lengths, cov)
     grid = torch.cuda.get_device_properties(0).multi_processor_count
     block = KEYS / ROWS * max(int(c.max()) for c in cov.values())
-    chunk = max(work / grid + 1, MIN_BLOCKS, block)
+    chunk = max(17 / 16 * work / grid + 1, MIN_BLOCKS, block)
     say(f"  {len(items)} items, {splits} cut, longest {longest:.1f} steps, C {chunk:.1f}")
     assert (splits > 0) == cut
     if cut:   # a cut lies within a key block of its place
